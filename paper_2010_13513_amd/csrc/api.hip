@@ -877,8 +877,28 @@ void op_smooth(hhg_hier h, int l, T* x, const T* b, int iters, int gs, int xi, d
     round_out<T>(h, l, x, lv.g.vstride, c < kGsVertexColours ? 0 : (size_t)(c - kGsVertexColours + 1) * lv.g.nn,
                  lv.g.nn, 3);
   };
+  const bool bf16_lv = std::is_same<T, float>::value && l - h->lmin < h->bf16_levels;
+  if (!lv.nu64 && !bf16_lv && gs_runs_supported(lv.g)) {
+    unsigned in_alt = 0;
+    for (int it = 0; it < iters; ++it) {
+      for (int s = 0; s < xi; ++s) {
+        launch_gs_sweep<T>(S(h), lv.g, lconst<T>(lv), x, r, b, false, in_alt);
+        if (gs == HHG_GS_SYM) launch_gs_sweep<T>(S(h), lv.g, lconst<T>(lv), x, r, b, true, in_alt);
+      }
+      PStep<T> ps;
+      ps.p = x + 3 * (size_t)lv.g.vstride;
+      ps.dinv = dinv<T>(lv);
+      ps.omega = (T)omega;
+      launch_apply<T>(S(h), lv.g, lconst<T>(lv), tables<T>(lv), in_alt ? r : x, b, r, full_mask(h), true, false, true,
+                      lv.bnd, lv.nbnd, ps);
+    }
+    if (in_alt) launch_scaled_copy<T>(S(h), x, r, nullptr, 3 * (size_t)lv.g.vstride, T(1));
+    return;
+  }
   for (int it = 0; it < iters; ++it) {
-    for (int s = 0; s < xi; ++s) {
+    const bool whole = !lv.nu64 && !bf16_lv &&
+                       launch_gs_level<T>(S(h), lv.g, lconst<T>(lv), x, b, xi, gs == HHG_GS_SYM);
+    for (int s = 0; s < (whole ? 0 : xi); ++s) {
       for (int c = 0; c < ncol; ++c) colour(c);
       if (gs == HHG_GS_SYM)
         for (int c = ncol - 1; c >= 0; --c) colour(c);

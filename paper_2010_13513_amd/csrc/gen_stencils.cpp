@@ -530,6 +530,151 @@ void emit_prolongation_cube(FILE* f, const char* D, int vorder) {
   std::fprintf(f, "    default: break;\n  }\n}\n\n");
 }
 
+// Rows over a box of the lattice held in LDS with compile-time strides: S1,
+// S2 the index strides of j and k, SG the stride between velocity groups, so
+// that every entry is an immediate offset of one address.  Integer weights in
+// units of 1 / {D}_zm_den (as in the k-marching rows).  A: the row of group g
+// at u (its own site); BT: component d of B^T p at p (the P1 node of the
+// site's index).  Two partial sums halve the dependent multiply-add chain.
+void emit_box_rows(FILE* f, const ElementSet& es, const char* D, int G) {
+  std::vector<double> wa, wt;
+  for (int r = 0; r < G; ++r) {
+    for (auto& e : pruned(es, 'A', r, 1)) wa.push_back(e.w[0]);
+    for (auto& e : pruned(es, 'T', r, 3))
+      for (int d = 0; d < 3; ++d) wt.push_back(e.w[d]);
+  }
+  const int da = common_den(wa), dt = common_den(wt);
+  for (int g = 0; g < G; ++g) {
+    std::fprintf(f,
+                 "template <typename T, int S1, int S2, int SG, typename P>\n__device__ __forceinline__ T %s_As_g%d(P u) {\n"
+                 "  T a = 0, b = 0;\n",
+                 D, g);
+    int q = 0;
+    for (auto& e : pruned(es, 'A', g, 1))
+      std::fprintf(f, "  %s = fma(T(%s), u[(%d) * SG + (%d) + (%d) * S1 + (%d) * S2], %s);\n", q & 1 ? "b" : "a",
+                   lit(std::nearbyint(e.w[0] * da)).c_str(), e.g - g, e.di, e.dj, e.dk, q & 1 ? "b" : "a"),
+          ++q;
+    std::fprintf(f, "  return a + b;\n}\n");
+    for (int d = 0; d < 3; ++d) {
+      std::fprintf(f,
+                   "template <typename T, int S1, int S2, typename P>\n__device__ __forceinline__ T %s_BTs_g%d_d%d(P p) {\n"
+                   "  T a = 0, b = 0;\n",
+                   D, g, d);
+      q = 0;
+      for (auto& e : pruned(es, 'T', g, 3)) {
+        if (std::fabs(e.w[d]) < 1e-13) continue;
+        std::fprintf(f, "  %s = fma(T(%s), p[(%d) + (%d) * S1 + (%d) * S2], %s);\n", q & 1 ? "b" : "a",
+                     lit(std::nearbyint(e.w[d] * dt)).c_str(), e.di, e.dj, e.dk, q & 1 ? "b" : "a");
+        ++q;
+      }
+      std::fprintf(f, "  return a + b;\n}\n");
+    }
+  }
+  std::fprintf(f, "template <typename T, int GR, int S1, int S2, int SG, typename P>\n__device__ __forceinline__ T %s_As(P u) {\n", D);
+  for (int g = 0; g < G; ++g) std::fprintf(f, "  if constexpr (GR == %d) return %s_As_g%d<T, S1, S2, SG>(u);\n", g, D, g);
+  std::fprintf(f, "}\ntemplate <typename T, int GR, int S1, int S2, typename P>\n__device__ __forceinline__ T %s_BTs(P p, int d) {\n", D);
+  for (int g = 0; g < G; ++g)
+    std::fprintf(f,
+                 "  if constexpr (GR == %d) return d == 0 ? %s_BTs_g%d_d0<T, S1, S2>(p) : (d == 1 ? %s_BTs_g%d_d1<T, S1, S2>(p) "
+                 ": %s_BTs_g%d_d2<T, S1, S2>(p));\n",
+                 g, D, g, D, g, D, g);
+  std::fprintf(f, "}\n\n");
+}
+
+// A run of Gauss-Seidel colours done on one box of the lattice (overlapped
+// tiles): `seq` lists the colours in order.  With the tile [0, t) per axis as
+// the sites whose final values are wanted, step s has to update its group on
+// [lo[s], t + hi[s]) -- wider than the tile where later steps read its
+// neighbours -- and group g has to be loaded on [glo, t + ghi), the pressure on
+// [plo, t + phi); all follow from the rows' offsets, backwards from the last
+// step.  wr[g]: the run updates group g; first[s]: vertex colours come in two
+// halves (parity par[s]).
+void emit_sequence(FILE* f, const ElementSet& es, int G, const std::string& name, const std::vector<int>& seq) {
+  struct Box {
+    bool any = false;
+    int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
+    void add(const int* l, const int* h) {
+      for (int d = 0; d < 3; ++d) {
+        lo[d] = any ? std::min(lo[d], l[d]) : l[d];
+        hi[d] = any ? std::max(hi[d], h[d]) : h[d];
+      }
+      any = true;
+    }
+  };
+  auto group = [&](int c) { return c < 2 ? 0 : c - 1; };
+  std::vector<Box> need(G), step(seq.size());
+  Box pb, all;
+  const int z[3] = {0, 0, 0}, one[3] = {1, 1, 1};
+  std::vector<int> wr(G, 0);
+  for (int c : seq) {
+    wr[group(c)] = 1;
+    need[group(c)].add(z, z);
+  }
+  for (int q = (int)seq.size() - 1; q >= 0; --q) {
+    const int g = group(seq[q]);
+    step[q] = need[g];
+    const Box r = step[q];
+    auto around = [&](const Entry& e, Box& b) {
+      const int o[3] = {e.di, e.dj, e.dk};
+      int l[3], h[3];
+      for (int d = 0; d < 3; ++d) l[d] = r.lo[d] + o[d], h[d] = r.hi[d] + o[d];
+      b.add(l, h);
+    };
+    for (auto& e : pruned(es, 'A', g, 1)) around(e, need[e.g]);
+    for (auto& e : pruned(es, 'T', g, 3)) around(e, pb);
+  }
+  for (int g = 0; g < G; ++g)
+    if (wr[g]) need[g].add(z, one);  // the upper boundary layer of the last tile is copied with it
+  for (int g = 0; g < G; ++g)
+    if (need[g].any) all.add(need[g].lo, need[g].hi);
+  all.add(pb.lo, pb.hi);
+  auto arr = [&](const int* v) {
+    return "{" + std::to_string(v[0]) + ", " + std::to_string(v[1]) + ", " + std::to_string(v[2]) + "}";
+  };
+  auto table = [&](const char* what, const std::vector<Box>& bs, bool hi) {
+    std::fprintf(f, "  static constexpr int %s[%zu][3] = {", what, bs.size());
+    for (auto& b : bs) std::fprintf(f, "%s, ", arr(hi ? b.hi : b.lo).c_str());
+    std::fprintf(f, "};\n");
+  };
+  std::fprintf(f, "struct %s {\n  static constexpr int n = %zu, G = %d;\n  static constexpr int col[%zu] = {", name.c_str(),
+               seq.size(), G, seq.size());
+  for (int c : seq) std::fprintf(f, "%d, ", c);
+  std::fprintf(f, "};\n  static constexpr int wr[%d] = {", G);
+  for (int g = 0; g < G; ++g) std::fprintf(f, "%d, ", wr[g]);
+  std::fprintf(f, "};\n  static constexpr int used[%d] = {", G);
+  for (int g = 0; g < G; ++g) std::fprintf(f, "%d, ", need[g].any ? 1 : 0);
+  std::fprintf(f, "};\n");
+  table("lo", step, false);
+  table("hi", step, true);
+  table("glo", need, false);
+  table("ghi", need, true);
+  std::fprintf(f, "  static constexpr int plo[3] = %s, phi[3] = %s, blo[3] = %s, bhi[3] = %s;\n};\n", arr(pb.lo).c_str(),
+               arr(pb.hi).c_str(), arr(all.lo).c_str(), arr(all.hi).c_str());
+}
+void emit_sequences(FILE* f, const ElementSet& es, int vorder) {
+  if (vorder == 2) {
+    // contiguous colour ranges a..b, forward and backward; the two vertex
+    // colours stay in one run
+    for (int a = 0; a <= 8; ++a)
+      for (int b = a; b <= 8; ++b) {
+        if (a == 1 || b == 0) continue;
+        std::vector<int> fw, bw;
+        for (int c = a; c <= b; ++c) fw.push_back(c);
+        bw.assign(fw.rbegin(), fw.rend());
+        emit_sequence(f, es, 8, "P2Fwd" + std::to_string(a) + std::to_string(b), fw);
+        emit_sequence(f, es, 8, "P2Bwd" + std::to_string(b) + std::to_string(a), bw);
+      }
+  } else {
+    // m colours in turn, starting with colour s
+    for (int s = 0; s < 2; ++s)
+      for (int m = 1; m <= 6; ++m) {
+        std::vector<int> q;
+        for (int i = 0; i < m; ++i) q.push_back((s + i) & 1);
+        emit_sequence(f, es, 1, "P1Seq" + std::to_string(s) + std::to_string(m), q);
+      }
+  }
+}
+
 double diag_of(const Row& r, int g) {
   for (auto& e : r)
     if (e.g == g && e.di == 0 && e.dj == 0 && e.dk == 0) return e.w[0];
@@ -581,6 +726,8 @@ int main(int argc, char** argv) {
       emit_pp(f, "p1_C", C);
     }
     emit_zm(f, es, D, G);
+    emit_box_rows(f, es, D, G);
+    emit_sequences(f, es, vorder);
     emit_boundary_rows(f, es, D, G);
     emit_restriction(f, D, vorder);
     if (vorder == 2) emit_restriction_zm(f, D, vorder);

@@ -189,6 +189,12 @@ void launch_apply(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const T
                   const PStep<T>& ps = PStep<T>{});
 template <typename T>
 void launch_gs_colour(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* b, int colour);
+bool gs_runs_supported(const Geom& g);
+template <typename T>
+bool launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* b, int xi, bool sym);
+template <typename T>
+void launch_gs_sweep(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* b, bool backward,
+                     unsigned& in_alt);
 template <typename T>
 void launch_pressure_step(hipStream_t s, const Geom& g, const T* dinv, T* x, const T* rp, T omega);
 template <typename T>

@@ -13,96 +13,12 @@
 
 #include "kernels.h"
 #include "lanes.h"
-
-namespace hhg {
-namespace gen {
-// One word of a buffer (raw buffer load, bounds-checked by the resource: an
-// offset outside it reads 0).
-template <typename T>
-__device__ __forceinline__ T buffer_word(__amdgpu_buffer_rsrc_t r, int voff, int soff);
-template <>
-__device__ __forceinline__ double buffer_word<double>(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
-}
-template <>
-__device__ __forceinline__ float buffer_word<float>(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-}
-// Buffer resource over n bytes from p (gfx9 word 3: 32-bit data format).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned n) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)n, 0x00020000);
-}
-}  // namespace gen
-}  // namespace hhg
-
-namespace hhg {
-namespace gen {
-// Order points of the k-marching plane step.  The compiler otherwise makes
-// the lane-shifted copies of every loaded word right after the loads and the
-// multiply-adds much later, holding all copies at once (about 40 registers).
-// An empty volatile asm that takes the accumulators (zm_order) and the next
-// word (zm_word) as in/out register operands fixes the order word by word:
-// it emits no instruction and touches no memory.
-template <typename T, int R>
-__device__ __forceinline__ void zm_order(T (&acc)[3][R]) {
-#pragma unroll
-  for (int s = 0; s < 3; ++s)
-#pragma unroll
-    for (int r = 0; r < R; ++r) asm volatile("" : "+v"(acc[s][r]));
-}
-template <typename T>
-__device__ __forceinline__ T zm_word(T v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-}  // namespace gen
-}  // namespace hhg
+#include "lattice.h"
 
 #include "generated/stencils.inc"
 
 namespace hhg {
 namespace {
-
-constexpr int kBlock = 256;
-
-__device__ __forceinline__ void decode(int t, int n1, int& i, int& j, int& k) {
-  i = t % n1;
-  const int r = t / n1;
-  j = r % n1;
-  k = r / n1;
-}
-// parity class of velocity group g (0: vertex, 1..7: edge directions)
-__device__ __forceinline__ int gdx(int g) { return (0xB2 >> g) & 1; }
-__device__ __forceinline__ int gdy(int g) { return (0xD4 >> g) & 1; }
-__device__ __forceinline__ int gdz(int g) { return (0xE8 >> g) & 1; }
-
-template <int G>
-__device__ __forceinline__ bool vel_interior(int g, int i, int j, int k, int N) {
-  const int dx = G == 1 ? 0 : gdx(g), dy = G == 1 ? 0 : gdy(g), dz = G == 1 ? 0 : gdz(g);
-  return i >= 1 - dx && j >= 1 - dy && k >= 1 - dz && i <= N - 1 && j <= N - 1 && k <= N - 1;
-}
-// velocity site exists (not padding): doubled position 2(i,j,k) + dir inside [0, 2N]
-template <int G>
-__device__ __forceinline__ bool vel_exists(int g, int i, int j, int k, int N) {
-  if (G == 1) return true;
-  return i + gdx(g) <= N && j + gdy(g) <= N && k + gdz(g) <= N;
-}
-__device__ __forceinline__ int bcls3(int c, int N) { return c == 0 ? 0 : (c == N ? 2 : 1); }
-
-// Faces of the cube a velocity site lies on (bit f as in Geom::nf), from its
-// position in site units (doubled for P2).
-__device__ __forceinline__ int site_faces(int X, int Y, int Z, int M) {
-  return (X == 0) | ((X == M) << 1) | ((Y == 0) << 2) | ((Y == M) << 3) | ((Z == 0) << 4) | ((Z == M) << 5);
-}
-// The velocity site is an unknown: it exists and lies on no Dirichlet face
-// (interior sites, and sites whose faces are all outflow faces).
-template <int G>
-__device__ __forceinline__ bool vel_unknown(const Geom& g, int gr, int i, int j, int k) {
-  if (!vel_exists<G>(gr, i, j, k, g.N)) return false;
-  const int f = G == 1 ? site_faces(i, j, k, g.N)
-                       : site_faces(2 * i + gdx(gr), 2 * j + gdy(gr), 2 * k + gdz(gr), 2 * g.N);
-  return (f & ~g.nf) == 0;
-}
 
 unsigned nblocks(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 

@@ -1,0 +1,48 @@
+"""Gauss-Seidel sweeps that run several colours per launch on boxes of the
+lattice in LDS (whole small levels, overlapped tiles on the middle levels):
+the smoother against the oracle's pointwise multicolour sweeps at every size
+with its own tiling, in both precisions, forward and symmetric, with an odd
+and an even number of sweeps (the tiles alternate between two buffers)."""
+import numpy as np
+import pytest
+
+from oracle import fe
+from oracle.smoother import Uzawa
+from oracle.stokes import Stokes
+from paper_2010_13513_amd import hhg
+from tests.gpu_util import Lib, assert_blocks
+
+pytestmark = pytest.mark.gpu
+
+P1, P2 = hhg.HHG_P1P1, hhg.HHG_P2P1
+_ORACLE = {}
+
+
+def _oracle(vorder, N):
+    if (vorder, N) not in _ORACLE:
+        _ORACLE[vorder, N] = Uzawa(Stokes(fe.Level(N, vorder)), "sd")
+    return _ORACLE[vorder, N]
+
+
+@pytest.mark.parametrize("gs,xi,iters", [(hhg.HHG_GS_FWD, 3, 1), (hhg.HHG_GS_FWD, 1, 2), (hhg.HHG_GS_SYM, 1, 1)])
+@pytest.mark.parametrize("disc,L", [(P1, 3), (P1, 4), (P2, 2), (P2, 3), (P2, 4), (P2, 5)])
+def test_smooth_boxes(disc, L, gs, xi, iters):
+    vorder = 1 if disc == P1 else 2
+    U = _oracle(vorder, 2 ** L)
+    n = U.S.n
+    rng = np.random.default_rng(13513 + 100 * L + vorder)
+    lib = Lib(disc, L - 1, L)
+    try:
+        for prec, rnd, tol in ((hhg.HHG_F64, lambda a: a, 1e-12),
+                               (hhg.HHG_F32, lambda a: a.astype(np.float32).astype(float), 500 * 2.0 ** -24)):
+            x, b = rnd(rng.standard_normal(n)), rnd(rng.standard_normal(n))
+            xd, bd = lib.from_lattice(L, x, prec), lib.from_lattice(L, b, prec)
+            hhg.hhg_smooth(lib.h, L, xd, bd, iters, gs, xi, 2.3, prec)
+            want = x
+            for _ in range(iters):
+                want = U.iterate(want, b, "s" if gs == hhg.HHG_GS_SYM else "f", xi, 1.0 / 2.3)
+            got = lib.to_lattice(L, xd, prec)
+            assert_blocks(lib, L, got, want, tol, f"smooth boxes xi {xi} iters {iters}")
+            assert np.array_equal(lib.to_lattice(L, bd, prec), b)
+    finally:
+        lib.close()
