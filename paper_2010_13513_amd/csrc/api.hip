@@ -1166,7 +1166,9 @@ void vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_para
     sc.nunk = h->nunk;
     sc.lds_words = (std::is_same<T, double>::value ? h->lds_end64 : h->lds_end32)[l - h->lmin];
     sc.q16 = std::is_same<T, float>::value ? h->bf16_levels : 0;
-    launch_vcycle_small<T>(S(h), slv<T>(h), sc);
+    bool var = false;
+    for (int q = h->lmin; q <= l; ++q) var = var || h->L(q).nu64;
+    if (!launch_cycle_small<T>(S(h), slv<T>(h), sc, h->L(l).g.N, var)) launch_vcycle_small<T>(S(h), slv<T>(h), sc);
     return;
   }
   Level& lv = h->L(l);

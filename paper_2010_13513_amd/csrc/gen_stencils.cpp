@@ -675,6 +675,42 @@ void emit_sequences(FILE* f, const ElementSet& es, int vorder) {
   }
 }
 
+// Pressure rows of all 27 boundary classes over one list of entries (the union
+// of the classes' entries): {D}_Pn entries, {D}_Poff their (group, di, dj, dk),
+// {D}_Pw[(cls n + e) m + c] the weights at h = 1 -- m = 3 components of B, and
+// for P1 a fourth, the P1 stiffness (C).  Entries a class does not have weigh
+// zero.
+void emit_class_rows(FILE* f, const ElementSet& es, const char* D, int G) {
+  const int rep[3] = {0, 2, 4};
+  auto same = [](const Entry& a, const Entry& b) { return a.g == b.g && a.di == b.di && a.dj == b.dj && a.dk == b.dk; };
+  std::vector<Row> B(27), C(27);
+  Row all;
+  for (int cls = 0; cls < 27; ++cls) {
+    const int ci = rep[cls % 3], cj = rep[(cls / 3) % 3], ck = rep[cls / 9];
+    B[cls] = pruned_at(es, 'B', ci, cj, ck, 3);
+    if (G == 1) C[cls] = pruned_at(es, 'C', ci, cj, ck, 1);
+    for (const Row* r : {&B[cls], &C[cls]})
+      for (auto& e : *r)
+        if (std::none_of(all.begin(), all.end(), [&](const Entry& a) { return same(a, e); })) all.push_back(e);
+  }
+  const int m = G == 1 ? 4 : 3;
+  std::fprintf(f, "constexpr int %s_Pn = %zu;\nconstexpr int %s_Poff[%zu][4] = {", D, all.size(), D, all.size());
+  for (auto& e : all) std::fprintf(f, "{%d, %d, %d, %d}, ", e.g, e.di, e.dj, e.dk);
+  std::fprintf(f, "};\nstatic __device__ const double %s_Pw[27 * %zu * %d] = {\n", D, all.size(), m);
+  for (int cls = 0; cls < 27; ++cls)
+    for (auto& a : all) {
+      double w[4] = {0, 0, 0, 0};
+      for (auto& e : B[cls])
+        if (same(a, e))
+          for (int d = 0; d < 3; ++d) w[d] = e.w[d];
+      for (auto& e : C[cls])
+        if (same(a, e)) w[3] = e.w[0];
+      for (int c = 0; c < m; ++c) std::fprintf(f, "%s, ", lit(w[c]).c_str());
+      std::fprintf(f, "\n");
+    }
+  std::fprintf(f, "};\n\n");
+}
+
 double diag_of(const Row& r, int g) {
   for (auto& e : r)
     if (e.g == g && e.di == 0 && e.dj == 0 && e.dk == 0) return e.w[0];
@@ -729,6 +765,7 @@ int main(int argc, char** argv) {
     emit_box_rows(f, es, D, G);
     emit_sequences(f, es, vorder);
     emit_boundary_rows(f, es, D, G);
+    emit_class_rows(f, es, D, G);
     emit_restriction(f, D, vorder);
     if (vorder == 2) emit_restriction_zm(f, D, vorder);
     emit_prolongation_cube(f, D, vorder);

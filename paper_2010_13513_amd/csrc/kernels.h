@@ -167,6 +167,10 @@ struct SmallCycle {
 constexpr int kSmallLdsBytes = 128 * 1024;
 template <typename T>
 void launch_vcycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc);
+// The same cycle by the kernel specialised on the top level's lattice size
+// (constant coefficients; false: not supported, nothing launched).
+template <typename T>
+bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc, int ntop, bool var);
 // Allow kSmallLdsBytes of dynamic LDS for the one-workgroup V-cycle kernels.
 void small_kernel_attributes();
 
