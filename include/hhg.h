@@ -419,9 +419,10 @@ hhg_status hhg_coarse_pair(hhg_hier h, const double* r, float* features, float* 
  * attached, the recorder on or coarse_smooth > 0).  Default 800; 0 turns it
  * off.  On an unstructured macro mesh the same bound is on a level's slots
  * (cells times points per cell) and applies to every smoothing call
- * (hhg_smooth and the smoothing inside cycles): one workgroup runs the whole
- * call, every value computed as by the per-colour launches; default 300
- * (the cube benchmark's level 1), meshes of at most 64 cells. */
+ * (hhg_smooth and the smoothing inside cycles) on levels of at most 20000
+ * nodes: the call runs on assembled rows of the nodes in one workgroup, or
+ * one per velocity component, instead of a launch per colour (same updates
+ * in the same order, the sums of a row in another order); default 30000. */
 hhg_status hhg_hier_set_fused_sites(hhg_hier h, long max_sites);
 /* Not in the paper: bfloat16 storage on the coarse levels of float32
  * cycles.  The n coarsest levels (lmin .. lmin + n - 1, 0 <= n <= number of

@@ -136,14 +136,13 @@ struct hhg_ctx_s {
 constexpr size_t kScratchEpochs = 4096;
 constexpr size_t kScratchOrder = (size_t)1 << 21;
 constexpr size_t kScratchBytes = kScratchEpochs * sizeof(double) + kScratchOrder * sizeof(int);
-// Default bound of the one-workgroup smoothing calls on unstructured meshes
-// (slots of a level; hhg_hier_set_fused_sites).  An interface node's update
-// is three dependent round trips (records, rows, own value), so one
-// workgroup only wins where a colour is a single pass of its threads: on
-// the cube benchmark (24 cells) level 1 (240 slots) gains, level 2 (840)
-// loses (FMG solve: off 26.4 ms, up to level 1 25.8, up to level 2 28.2,
-// up to level 3 47.6).
-constexpr long kUFusedSlots = 300;
+// Default bound of the node-table smoothing calls on unstructured meshes
+// (slots of a level; hhg_hier_set_fused_sites): every level that has the
+// tables gains.  FMG(2,3,2,1,A_s,1) on the cube benchmark to level 6, with
+// them up to no level 26.3 ms, level 1 22.9, 2 18.5, 3 14.8, 4 13.4; per Uzawa
+// iteration (A_s, xi = 1) level 1 69 -> 11 us, 2 130 -> 18, 3 145 -> 32, 4 165
+// -> 80.
+constexpr long kUFusedSlots = 30000;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 // Macro mesh T_0 (host data): vertex coordinates, tetrahedra, and the number
@@ -196,7 +195,7 @@ struct hhg_hier_s {
   bool slv_stale = true;
   long fused_sites = 800;
   // unstructured meshes: levels with at most ufused_slots slots (cells times
-  // points per cell) run each smoothing call in one workgroup (0: never)
+  // points per cell) run each smoothing call on their node tables (0: never)
   long ufused_slots = kUFusedSlots;
   std::vector<int> lds_end64, lds_end32;  // LDS words of levels lmin..l (0: level not in LDS)
   // levels lmin .. lmin + bf16_levels - 1 hold bfloat16 values in their
@@ -732,7 +731,7 @@ void u_smooth(hhg_hier h, int l, double* x, const double* b, int iters, int gs, 
   const int ncol = U.ncol_if + 4;
   double* r = h->L(l).r;
   if ((long)U.L.ncell * U.L.P <= h->ufused_slots &&
-      launch_u_smooth_small(S(h), U, x, b, r, iters, xi, gs == HHG_GS_SYM, omega))
+      launch_u_smooth_nodes(S(h), U, x, b, iters, xi, gs == HHG_GS_SYM, omega))
     return;
   for (int it = 0; it < iters; ++it) {
     for (int s = 0; s < xi; ++s) {
@@ -1443,6 +1442,7 @@ hhg_hier u_hier_create(hhg_mesh mesh, hhg_disc disc, int lmin, int lmax, hhg_sch
   h->nf = mesh->outflow.empty() ? 0 : 1;  // the pressure is determined: no mean-zero steps
   h->um.reset(u_build(mesh->xyz.data(), (int)(mesh->xyz.size() / 3), mesh->tet.data(), (int)(mesh->tet.size() / 4),
                       mesh->outflow, lmin, lmax, schur));
+  u_kernel_attributes();
   h->partial = h->arena.alloc<double>(4 * kPartials);
   h->sums = h->arena.alloc<double>(16);
   HHG_CHECK_HIP(hipHostMalloc((void**)&h->hsums, 16 * sizeof(double), hipHostMallocDefault));

@@ -9,7 +9,8 @@
 // lanes per node, one per stencil point and occurrence slot: the row is the
 // sum, over the cells containing the node, of that cell's row of the node's
 // class, and the result goes to every copy of the node.  The smoothing calls
-// of the smallest levels run in one workgroup (k_u_smooth_small).
+// of the smallest levels run in one workgroup on assembled rows
+// (k_u_smooth_nodes).
 #include <type_traits>
 
 #include "lanes.h"
@@ -709,123 +710,273 @@ __global__ void __launch_bounds__(kUBlock) k_u_sync(ULev L, UList lst, double* _
 unsigned ublocks(long n) { return (unsigned)((n + kUBlock - 1) / kUBlock); }
 
 // ---------------------------------------------------------- small levels
-// One workgroup runs a whole smoothing call (iters Uzawa iterations, Sec.
-// 3.2) on a small level: the phases of the launch-per-colour path -- every
-// interface colour, then the four interior colours (xi sweeps, each also
-// reversed for the symmetric variant), the pressure residual rows, the
-// pressure step -- each a block-strided loop over the same per-node and
-// per-point functions with the same lanes per node, phases separated by
-// workgroup barriers, so every value is computed as there.  The cells'
-// interior rows are staged in LDS once.  On the small levels a launch per
-// phase is almost all launch latency.
-constexpr int kUSmall = 1024;
-constexpr int kUSmallCells = 64;  // LDS: 8 x 15 words per cell
+// Smoothing by nodes (UNodes): every node once, its row assembled over the
+// cells, so a row is a batch of independent loads and one gather from LDS --
+// the cell-by-cell rows of the launch-per-colour path are three dependent
+// round trips per node and a launch per colour.
+constexpr int kUNodeLds = 160 * 1024 - 1024;  // dynamic LDS of one workgroup
 
-struct USmallArgs {
-  ULev L;
-  UList lst;
-  USegs inner, colour[4];
-  const int* col_off;  // K + 1 offsets of the interface colours
-  const int* col_sl;   // K occurrence slots per interface colour
-  int K, list_sl;      // list_sl: occurrence slots of the whole list (residual rows)
-  const double* dinv;
-  double omega;
-  int iters, xi, sym;
-};
-
-template <int SL>
-__device__ void small_gs_iface(const ULev& L, const UList& lst, int first, int count, double* __restrict__ x,
-                               const double* __restrict__ b) {
-  constexpr int GW = kIfPts * SL;
-  for (int t0 = 0; t0 < count; t0 += kUSmall / GW) {
-    const int t = t0 + (int)threadIdx.x / GW;
-    if (t < count) gs_iface_node<SL>(L, lst, first + t, (int)threadIdx.x % GW, x, b);
-  }
+// E entries (E even) of a node's rows: columns.
+template <int E>
+__device__ __forceinline__ void node_cols(const unsigned* __restrict__ col, int n, unsigned (&k)[E / 2]) {
+#pragma unroll
+  for (int e = 0; e < E / 2; ++e) k[e] = col[e * n];
 }
-template <int SL>
-__device__ void small_presid_iface(const ULev& L, const UList& lst, const double* __restrict__ x,
-                                   const double* __restrict__ b, double* __restrict__ r) {
-  constexpr int GW = kIfPts * SL;
-  for (int t0 = 0; t0 < lst.n; t0 += kUSmall / GW) {
-    const int q = t0 + (int)threadIdx.x / GW;
-    if (q < lst.n) apply_iface_node<true, false, SL>(L, lst, q, (int)threadIdx.x % GW, x, b, r, 12, 0, 1);
-  }
+__device__ __forceinline__ int node_col(const unsigned* k, int e) {
+  return (int)(e & 1 ? k[e >> 1] >> 16 : k[e >> 1] & 0xffffu);
+}
+// a += sum_e w[e] v[column e] of entries e0 .. e0 + E.
+template <int E>
+__device__ __forceinline__ double node_row(const double* __restrict__ w, const unsigned* __restrict__ col, int n,
+                                           const double* v, double a) {
+  double we[E];
+  unsigned k[E / 2];
+  node_cols<E>(col, n, k);
+#pragma unroll
+  for (int e = 0; e < E; ++e) we[e] = w[e * n];
+#pragma unroll
+  for (int e = 0; e < E; ++e) a = fma(we[e], v[node_col(k, e)], a);
+  return a;
+}
+// Row of q over its first 16 entries and, below `more` entries, the rest.
+__device__ __forceinline__ double node_row_len(const double* __restrict__ w, const unsigned* __restrict__ col, int n,
+                                               int len, const double* v) {
+  double a = node_row<16>(w, col, n, v, 0.0);
+#pragma unroll 1
+  for (int e = 16; e < len; e += 8) a = node_row<8>(w + e * n, col + (e / 2) * n, n, v, a);
+  return a;
+}
+// f - B^T p at free node q, component d.
+__device__ __forceinline__ double node_rhs(const UNodes& N, const unsigned* __restrict__ col, int d, int q, double f,
+                                           const double* p) {
+  return f - node_row_len(N.BT + (size_t)d * N.len * N.n + q, col + q, N.n, q < N.off[N.ncol - 4] ? N.len : 16, p);
+}
+// B u (v = u_d, s = d < 3) or C p (s = 3) at node q.
+__device__ __forceinline__ double node_pres(const UNodes& N, const unsigned* __restrict__ col, int s, int q,
+                                            const double* v) {
+  const bool inner = q >= N.off[N.ncol - 4] && q < N.off[N.ncol];
+  return node_row_len((s < 3 ? N.B + (size_t)s * N.len * N.n : N.C) + q, col + q, N.n, inner ? 16 : N.len, v);
 }
 
-__global__ void __launch_bounds__(kUSmall) k_u_smooth_small(USmallArgs a, double* __restrict__ x,
-                                                            const double* __restrict__ b, double* __restrict__ r) {
-  extern __shared__ double wall[];  // [cell][8][15]: A, B^T (3), B (3), M of class 0
-  const ULev& L = a.L;
-  const int ncell = L.ncell;
-  for (int t = threadIdx.x; t < ncell * 8 * kUPoints; t += kUSmall) {
-    const int c = t / (8 * kUPoints), q = (t / kUPoints) % 8, e = t % kUPoints;
-    const UCell* cs = L.cs + c;
-    double v;
-    if (q == 0) v = cs->A[0][e];
-    else if (q < 4) v = cs->BT[0][e][q - 1];
-    else if (q < 7) v = cs->B[0][e][q - 4];
-    else v = cs->M[0][e];
-    wall[t] = v;
+// The smallest levels: the whole call in one workgroup, u, p, f - B^T p and
+// the A rows in LDS.  Wavefront d < 3 runs the sweeps of component d: no
+// coupling to the others, so its colours follow each other in program order
+// without a barrier; colour k + 1's row entries (and the schedule word of
+// k + 2) are read from LDS before colour k's update.  All wavefronts share the
+// B^T and pressure rows.
+constexpr int kUSmall = 512;
+__global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, long nslots, double* __restrict__ x,
+                                                            const double* __restrict__ b, int iters, int xi, int sym,
+                                                            double omega) {
+  extern __shared__ double lds[];
+  const int n = N.n, tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+  double* const u = lds;          // 3 n velocity, then n pressure
+  double* const p = lds + 3 * n;
+  double* const g = lds + 4 * n;  // 4 n: f - B^T p / the pressure rows' parts
+  double* const ai = lds + 8 * n;
+  double* const la = lds + 9 * n;
+  unsigned* const lc = reinterpret_cast<unsigned*>(la + (size_t)N.len * n);
+  int* const sched = reinterpret_cast<int*>(lc + (size_t)(N.len / 2) * n);  // one period: first | count << 12 | len << 24
+  const int per = sym ? 2 * N.ncol : N.ncol;
+  for (int t = tid; t < 4 * n; t += kUSmall) {
+    const int f = t / n, q = t - f * n;
+    u[t] = x[f * vs + N.own[q]];
+  }
+  for (int t = tid; t < n; t += kUSmall) ai[t] = N.ainv[t];
+  for (int t = tid; t < N.len * n; t += kUSmall) la[t] = N.A[t];
+  for (int t = tid; t < N.len / 2 * n; t += kUSmall) lc[t] = N.col[t];
+  if (tid < per) {
+    const int c = tid < N.ncol ? tid : per - 1 - tid;
+    sched[tid] = N.off[c] | (N.off[c + 1] - N.off[c]) << 12 | N.clen[c] << 24;
   }
   __syncthreads();
-  auto rows = [&](int c) { return reinterpret_cast<const double(*)[kUPoints]>(wall + c * 8 * kUPoints); };
-  auto colour = [&](int c) {
-    if (c < a.K) {
-      const int first = a.col_off[c], count = a.col_off[c + 1] - first, sl = a.col_sl[c];
-      if (sl == 1)
-        small_gs_iface<1>(L, a.lst, first, count, x, b);
-      else if (sl == 2)
-        small_gs_iface<2>(L, a.lst, first, count, x, b);
-      else
-        small_gs_iface<4>(L, a.lst, first, count, x, b);
-    } else {
-      const USegs sg = a.colour[c - a.K];
-      const int lps = sg.lps, tot = ncell * sg.n;
-      for (int w0 = 0; w0 < tot; w0 += kUSmall / lps) {
-        const int w = w0 + (int)threadIdx.x / lps, lane = (int)threadIdx.x % lps;
-        if (w < tot) {
-          const int cc = w / sg.n;
-          const int4 s = sg.s[w - cc * sg.n];
-          if (lane < s.w) gs_inner_pt(L, cc, rows(cc), L.cs[cc].ainv0, s.x + 4 * lane, s.y, s.z, x, b);
+#pragma unroll 1
+  for (int it = 0; it < iters; ++it) {
+    for (int t = tid; t < 3 * N.nfree; t += kUSmall) {
+      const int d = t / N.nfree, q = t - d * N.nfree;
+      g[d * n + q] = node_rhs(N, lc, d, q, b[d * vs + N.own[q]], p);
+    }
+    __syncthreads();
+    if (wave < 3) {
+      double* const ud = u + wave * n;
+      const double* const gd = g + wave * n;
+      const int steps = xi * per;
+      double w[16];
+      unsigned k[8];
+      auto fetch = [&](int s) {
+        const int q = (s & 4095) + min(lane, max(((s >> 12) & 4095) - 1, 0));
+        node_cols<16>(lc + q, n, k);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) w[e] = la[e * n + q];
+      };
+      int s0 = sched[0], s1 = sched[1 % per], r = 1 % per;
+      fetch(s0);
+#pragma unroll 1
+      for (int st = 0; st < steps; ++st) {
+        r = r + 1 < per ? r + 1 : 0;
+        const int s2 = sched[r];
+        const int q0 = s0 & 4095, m = (s0 >> 12) & 4095, len = s0 >> 24;
+        double a = 0.0, c = 0.0;
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          a = fma(w[e], ud[node_col(k, e)], a);
+          c = fma(w[e + 1], ud[node_col(k, e + 1)], c);
         }
+        fetch(s1);
+        if (lane < m) {
+          const int q = q0 + lane;
+          a += c;
+          for (int e = 16; e < len; e += 8) a = node_row<8>(la + e * n + q, lc + (e / 2) * n + q, n, ud, a);
+          ud[q] += (gd[q] - a) * ai[q];
+        }
+        for (int t = lane + 64; t < m; t += 64) {
+          const int q = q0 + t;
+          ud[q] += (gd[q] - node_row_len(la + q, lc + q, n, len, ud)) * ai[q];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        s0 = s1;
+        s1 = s2;
       }
     }
     __syncthreads();
-  };
-  const int ncol = a.K + 4;
-  for (int it = 0; it < a.iters; ++it) {
-    for (int sw = 0; sw < a.xi; ++sw) {
-      for (int c = 0; c < ncol; ++c) colour(c);
-      if (a.sym)
-        for (int c = ncol - 1; c >= 0; --c) colour(c);
+    // r_p = g - B u + C p, p -= omega D^{-1} r_p
+    for (int t = tid; t < 4 * n; t += kUSmall) {
+      const int s = t / n, q = t - s * n;
+      g[t] = node_pres(N, lc, s, q, u + s * n);
     }
-    // r_p = g - B u + C p: interior points and interface nodes (disjoint slots)
-    {
-      const USegs sg = a.inner;
-      const int lps = sg.lps, tot = ncell * sg.n;
-      for (int w0 = 0; w0 < tot; w0 += kUSmall / lps) {
-        const int w = w0 + (int)threadIdx.x / lps, lane = (int)threadIdx.x % lps;
-        if (w < tot) {
-          const int cc = w / sg.n;
-          const int4 s = sg.s[w - cc * sg.n];
-          if (lane < s.w)
-            apply_inner_pt<true, false>(L, cc, rows(cc), L.cs[cc].cfac, s.x + lane, s.y, s.z, x, b, r, 12, 0, 1);
-        }
-      }
-    }
-    if (a.list_sl == 1)
-      small_presid_iface<1>(L, a.lst, x, b, r);
-    else if (a.list_sl == 2)
-      small_presid_iface<2>(L, a.lst, x, b, r);
-    else
-      small_presid_iface<4>(L, a.lst, x, b, r);
     __syncthreads();
-    // p -= omega r_p D^-1 on every slot
-    const long ns = (long)ncell * L.P;
-    for (long t = threadIdx.x; t < ns; t += kUSmall) x[3 * L.vs + t] -= a.omega * r[3 * L.vs + t] * a.dinv[t];
+    for (int q = tid; q < n; q += kUSmall)
+      p[q] -= omega * (b[3 * vs + N.own[q]] - (g[q] + g[n + q] + g[2 * n + q] - g[3 * n + q])) * N.dinv[q];
     __syncthreads();
   }
+  for (long t = tid; t < nslots; t += kUSmall) {
+    const int q = N.node[t];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) x[f * vs + t] = u[f * n + q];
+  }
 }
+
+// Larger ones: the call on compact node arrays (N.work), per Uzawa iteration
+// the right-hand sides and the pressure step as launches over the nodes and
+// the sweeps as one launch of a workgroup per component with the component
+// in LDS.  Bound by the A rows' way from the L2 into one compute unit: the
+// interiors' weights are their cell's, staged in LDS once, so only their
+// columns are read.
+constexpr int kUSweep = 1024;
+__global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __restrict__ un,
+                                                           const double* __restrict__ gn, int xi, int sym) {
+  extern __shared__ double lds[];
+  const int n = N.n, tid = threadIdx.x, K = N.ncol - 4, in0 = N.off[K];
+  double* const u = lds;
+  double* const cw = lds + n;  // [cell][16]
+  double* const xu = un + (size_t)blockIdx.x * n;
+  const double* const g = gn + (size_t)blockIdx.x * n;
+  for (int t = tid; t < n; t += kUSweep) u[t] = xu[t];
+  for (int t = tid; t < 16 * N.ncell; t += kUSweep) cw[t] = N.cellA[t];
+  __syncthreads();
+  // the update of a colour needs, besides u, words that no sweep changes:
+  // they are loaded for the next colour before this colour's barrier
+  double w[16], ai = 0.0, gq = 0.0;
+  unsigned k[8];
+  int cl = 0;
+  auto fetch = [&](int c) {
+    const int q = N.off[c] + tid;
+    if (q < N.off[c + 1]) {
+      node_cols<16>(N.col + q, n, k);
+      if (c < K) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) w[e] = N.A[e * n + q];
+      } else {
+        cl = N.cell[q - in0];
+      }
+      ai = N.ainv[q];
+      gq = g[q];
+    }
+  };
+  const int per = sym ? 2 * N.ncol : N.ncol, steps = xi * per;
+  fetch(0);
+  int r = 0;
+#pragma unroll 1
+  for (int st = 0; st < steps; ++st) {
+    const int c = r < N.ncol ? r : per - 1 - r;
+    r = r + 1 < per ? r + 1 : 0;
+    const int cn = r < N.ncol ? r : per - 1 - r;
+    const int q0 = N.off[c], m = N.off[c + 1] - q0, len = N.clen[c];
+    double a = 0.0, a1 = 0.0;
+    if (tid < m) {
+      if (c >= K) {
+        const double* wc = cw + 16 * cl;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) w[e] = wc[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        a = fma(w[e], u[node_col(k, e)], a);
+        a1 = fma(w[e + 1], u[node_col(k, e + 1)], a1);
+      }
+      const int q = q0 + tid;
+      a += a1;
+      for (int e = 16; e < len; e += 8) a = node_row<8>(N.A + e * n + q, N.col + (e / 2) * n + q, n, u, a);
+      u[q] += (gq - a) * ai;
+    }
+    for (int t = tid + kUSweep; t < m; t += kUSweep) {
+      const int q = q0 + t;
+      double v;
+      if (c >= K) {
+        unsigned kk[8];
+        node_cols<16>(N.col + q, n, kk);
+        const double* wc = cw + 16 * N.cell[q - in0];
+        v = 0.0;
+#pragma unroll
+        for (int e = 0; e < 15; ++e) v = fma(wc[e], u[node_col(kk, e)], v);
+      } else {
+        v = node_row_len(N.A + q, N.col + q, n, len, u);
+      }
+      u[q] += (g[q] - v) * N.ainv[q];
+    }
+    if (st + 1 < steps) fetch(cn);
+    __syncthreads();
+  }
+  for (int t = tid; t < N.nfree; t += kUSweep) xu[t] = u[t];
+}
+// u, p of every node from its owner slot.
+__global__ void __launch_bounds__(kUBlock) k_u_nodes_gather(UNodes N, long vs, const double* __restrict__ x) {
+  const int q = blockIdx.x * kUBlock + threadIdx.x;
+  if (q >= N.n) return;
+  const int o = N.own[q];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) N.work[(size_t)f * N.n + q] = x[f * vs + o];
+}
+__global__ void __launch_bounds__(kUBlock) k_u_nodes_rhs(UNodes N, long vs, const double* __restrict__ b,
+                                                         const double* __restrict__ p, double* __restrict__ g) {
+  const int q = blockIdx.x * kUBlock + threadIdx.x, d = blockIdx.y;
+  if (q < N.nfree) g[(size_t)d * N.n + q] = node_rhs(N, N.col, d, q, b[d * vs + N.own[q]], p);
+}
+// pn = p - omega D^{-1} (g - B u + C p); four lanes per node, one per slice.
+__global__ void __launch_bounds__(kUBlock) k_u_nodes_pres(UNodes N, long vs, const double* __restrict__ b,
+                                                          const double* __restrict__ un, const double* __restrict__ p,
+                                                          double* __restrict__ pn, double omega) {
+  const int s = threadIdx.x / 64, q = blockIdx.x * 64 + (int)threadIdx.x % 64;
+  __shared__ double part[4][64];
+  part[s][threadIdx.x % 64] = q < N.n ? node_pres(N, N.col, s, q, s < 3 ? un + (size_t)s * N.n : p) : 0.0;
+  __syncthreads();
+  if (s || q >= N.n) return;
+  const int l = threadIdx.x;
+  const double r = b[3 * vs + N.own[q]] - (part[0][l] + part[1][l] + part[2][l] - part[3][l]);
+  pn[q] = p[q] - omega * r * N.dinv[q];
+}
+// Every slot from its node.
+__global__ void __launch_bounds__(kUBlock) k_u_nodes_scatter(UNodes N, long vs, long nslots,
+                                                             const double* __restrict__ p, double* __restrict__ x) {
+  const long t = (long)blockIdx.x * kUBlock + threadIdx.x;
+  if (t >= nslots) return;
+  const int q = N.node[t];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) x[d * vs + t] = N.work[(size_t)d * N.n + q];
+  x[3 * vs + t] = p[q];
+}
+
 dim3 seg_grid(const USegs& s, int ncell) {
   const int per = kUBlock / s.lps;
   return dim3((unsigned)((s.n + per - 1) / per), (unsigned)ncell);
@@ -914,28 +1065,38 @@ void launch_u_gs_iface(hipStream_t s, const ULev& L, const UList& lst, int first
   });
 }
 
-bool launch_u_smooth_small(hipStream_t s, const ULevelData& U, double* x, const double* b, double* r, int iters,
-                           int xi, bool sym, double omega) {
-  if (U.L.ncell > kUSmallCells || U.ncol_if > 64 || !U.col_off_d) return false;
+bool launch_u_smooth_nodes(hipStream_t s, const ULevelData& U, double* x, const double* b, int iters, int xi,
+                           bool sym, double omega) {
+  const UNodes& N = U.nodes;
+  const long vs = U.L.vs, slots = real_slots(U.L);
+  if (N.n == 0) return false;
   if (iters <= 0) return true;
-  KScope ks(s, KF_SMALL, (double)real_slots(U.L));
-  USmallArgs a{};
-  a.L = U.L;
-  a.lst = U.lst;
-  a.inner = U.inner;
-  for (int c = 0; c < 4; ++c) a.colour[c] = U.colour[c];
-  a.col_off = U.col_off_d;
-  a.col_sl = U.col_sl_d;
-  a.K = U.ncol_if;
-  a.list_sl = if_slots(U.lst.maxocc, U.lst.n);
-  a.dinv = U.dinv;
-  a.omega = omega;
-  a.iters = iters;
-  a.xi = xi;
-  a.sym = sym;
-  const size_t lds = (size_t)U.L.ncell * 8 * kUPoints * sizeof(double);
-  hipLaunchKernelGGL(k_u_smooth_small, dim3(1), dim3(kUSmall), lds, s, a, x, b, r);
+  KScope ks(s, KF_SMALL, (double)slots);
+  const size_t one = (size_t)N.n * (9 * sizeof(double) + N.len * (sizeof(double) + sizeof(unsigned) / 2)) +
+                     2 * kUNodeColours * sizeof(int);
+  if (one <= (size_t)kUNodeLds && N.n < 4096) {
+    hipLaunchKernelGGL(k_u_smooth_nodes, dim3(1), dim3(kUSmall), one, s, N, vs, slots, x, b, iters, xi, (int)sym,
+                       omega);
+    return true;
+  }
+  const size_t lds = ((size_t)N.n + 16 * N.ncell) * sizeof(double);
+  if (lds > (size_t)kUNodeLds) return false;
+  const size_t n = N.n;
+  double *u = N.work, *p = u + 3 * n, *pn = u + 4 * n, *g = u + 5 * n;
+  const dim3 blk(kUBlock);
+  hipLaunchKernelGGL(k_u_nodes_gather, dim3(ublocks(N.n)), blk, 0, s, N, vs, x);
+  for (int it = 0; it < iters; ++it) {
+    hipLaunchKernelGGL(k_u_nodes_rhs, dim3(ublocks(N.nfree), 3), blk, 0, s, N, vs, b, p, g);
+    hipLaunchKernelGGL(k_u_nodes_sweep, dim3(3), dim3(kUSweep), lds, s, N, u, g, xi, (int)sym);
+    hipLaunchKernelGGL(k_u_nodes_pres, dim3((N.n + 63) / 64), blk, 0, s, N, vs, b, u, p, pn, omega);
+    std::swap(p, pn);
+  }
+  hipLaunchKernelGGL(k_u_nodes_scatter, dim3(ublocks(slots)), blk, 0, s, N, vs, slots, p, x);
   return true;
+}
+void u_kernel_attributes() {
+  (void)hipFuncSetAttribute((const void*)k_u_smooth_nodes, hipFuncAttributeMaxDynamicSharedMemorySize, kUNodeLds);
+  (void)hipFuncSetAttribute((const void*)k_u_nodes_sweep, hipFuncAttributeMaxDynamicSharedMemorySize, kUNodeLds);
 }
 
 void launch_u_pstep(hipStream_t s, const ULev& L, const double* dinv, double* x, const double* r, double omega) {

@@ -87,6 +87,30 @@ struct USegs {
   int lps;
 };
 
+// A small level by nodes (each node once, no copies), for its smoothing calls:
+// local order = free interface nodes by colour, cell interiors by colour,
+// Dirichlet nodes.  Rows assembled over the cells, `len` entries each (a
+// multiple of 8, at least 16), entry-major ([e n + q]; unused entries: the
+// node itself with weight 0): A, B^T and B (three components each) and the
+// pressure block C; columns two to a word (entry 2 e in the low half of
+// col[e n + q]).  An interior node's entries are its 15 stencil points in
+// order, so its A weights are its cell's.  n = 0: the level has no tables.
+constexpr int kUNodeMax = 20000;
+constexpr int kUNodeColours = 64;
+struct UNodes {
+  int n = 0, nfree = 0, len = 0, ncol = 0, ncell = 0;
+  int off[kUNodeColours + 1];       // colour c: nodes off[c] .. off[c + 1]; the last four: cell interiors
+  int clen[kUNodeColours];          // its longest row, a multiple of 8, at least 16
+  const unsigned* col = nullptr;
+  const double *A = nullptr, *BT = nullptr, *B = nullptr, *C = nullptr;
+  const double* cellA = nullptr;    // [cell][16] interior A rows (entry 15: 0)
+  const unsigned short* cell = nullptr;  // cell of interior node off[ncol - 4] + i
+  const double *ainv = nullptr, *dinv = nullptr;
+  const int* own = nullptr;              // owner slot of a node
+  const unsigned short* node = nullptr;  // node of a slot
+  double* work = nullptr;                // 8 n: velocity (3), pressure (2), f - B^T p (3)
+};
+
 // Host-side state of one level of an unstructured hierarchy.
 struct ULevelData {
   ULev L{};
@@ -94,8 +118,7 @@ struct ULevelData {
   int ncol_if = 0;               // interface colours K (colours K..K+3: cell interiors)
   std::vector<int> col_off;      // K + 1 offsets into the free interface nodes
   std::vector<int> col_maxocc;   // per interface colour: most occurrences of one of its nodes
-  int* col_off_d = nullptr;      // device copies: col_off, occurrence slots per colour (if_slots)
-  int* col_sl_d = nullptr;
+  UNodes nodes;                  // small levels
   UList lst{};
   USegs all{}, inner{}, colour[4]{};
   USegs zitems{};                // k-marching items (j, i0, ka, kb) of the interior apply
@@ -130,12 +153,12 @@ void launch_u_gs_iface(hipStream_t s, const ULev& L, const UList& lst, int first
                        const double* b);
 void launch_u_pstep(hipStream_t s, const ULev& L, const double* dinv, double* x, const double* r, double omega);
 // A whole smoothing call (iters Uzawa iterations: xi sweeps of every colour,
-// also reversed when sym, then r_p = g - B u + C p into r and the pressure
-// step) in one workgroup, every value computed as by the per-colour
-// launches; false (nothing launched) when the level has more cells or
-// colours than the kernel holds.
-bool launch_u_smooth_small(hipStream_t s, const ULevelData& U, double* x, const double* b, double* r, int iters,
-                           int xi, bool sym, double omega);
+// also reversed when sym, then the pressure step) on the level's node tables;
+// false (nothing launched) when the level has none.
+bool launch_u_smooth_nodes(hipStream_t s, const ULevelData& U, double* x, const double* b, int iters, int xi,
+                           bool sym, double omega);
+// Allow the dynamic LDS of its kernels.
+void u_kernel_attributes();
 void launch_u_restrict(hipStream_t s, const ULev& Lf, const ULev& Lc, USegs inner_c, const UList& lst_c,
                        const double* rf, double* rc);
 void launch_u_prolong(hipStream_t s, const ULev& Lc, const ULev& Lf, USegs all_f, const double* xc, double* xf,

@@ -607,6 +607,117 @@ void u_level_host(const UMeshPrims& M, const double* xyz, int l, int schur, ULev
   lv.L.vs = vs;
 }
 
+// Node tables of a small level (UNodes): assembled rows of every node.
+void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
+  const int n = lv.L.n, nn = lv.nnodes, ncol = lv.ncol_if + 4;
+  if (nn > kUNodeMax || ncol > kUNodeColours || lv.L.ncell > 4096) return;
+  UNodes& N = lv.nodes;
+  struct Entry {
+    int r;
+    double a, bt[3], b[3], c;
+  };
+  auto slot_of = [&](const int2& o) {
+    return (long)o.x * lv.L.P + uslot(o.y & 1023, (o.y >> 10) & 1023, o.y >> 20, n);
+  };
+  // local order, and the occurrences of every node
+  std::vector<std::vector<int2>> occ;
+  occ.reserve(nn);
+  auto iface = [&](int t) {
+    occ.emplace_back(lv.h_occ.begin() + lv.h_off[t], lv.h_occ.begin() + lv.h_off[t + 1]);
+  };
+  for (int t = 0; t < H.nfree; ++t) iface(t);
+  for (int c = 0; c <= lv.ncol_if; ++c) N.off[c] = lv.col_off[c];
+  for (int c = 0; c < 4; ++c) {
+    for (int cell = 0; cell < lv.L.ncell; ++cell)
+      for (int k = 1; k <= n; ++k)
+        for (int j = k + 1; j <= n; ++j)
+          for (int i = j + 1; i <= n - 1; ++i)
+            if (((i + j + k) & 3) == c) occ.push_back({int2{cell, upack(i, j, k)}});
+    N.off[lv.ncol_if + 1 + c] = (int)occ.size();
+  }
+  N.nfree = (int)occ.size();
+  for (int t = H.nfree; t < H.nlist; ++t) iface(t);
+  HHG_REQUIRE((int)occ.size() == nn, HHG_ERR_STATE, "internal: node tables");
+  std::vector<int> local(nn, -1), own(nn);
+  for (int q = 0; q < nn; ++q) {
+    own[q] = (int)slot_of(occ[q][0]);
+    local[H.canon[own[q]]] = q;
+  }
+  std::vector<std::vector<Entry>> rows(nn);
+  size_t longest = 1;
+  for (int q = 0; q < nn; ++q) {
+    for (const int2& o : occ[q]) {
+      const int i = o.y & 1023, j = (o.y >> 10) & 1023, k = o.y >> 20, m = uclass(i, j, k, n);
+      const UCell& cs = lv.hcs[o.x];
+      for (int e = 0; e < kUPoints; ++e) {
+        if (!((cs.inside[m] >> e) & 1)) continue;
+        const int r = local[H.canon[(long)o.x * lv.L.P + uslot(i + udir(e, 0), j + udir(e, 1), k + udir(e, 2), n)]];
+        size_t w = 0;
+        while (w < rows[q].size() && rows[q][w].r != r) ++w;
+        if (w == rows[q].size()) rows[q].push_back(Entry{r, 0.0, {0, 0, 0}, {0, 0, 0}, 0.0});
+        Entry& en = rows[q][w];
+        en.a += cs.A[m][e];
+        en.c += cs.cfac * cs.A[m][e];
+        for (int d = 0; d < 3; ++d) {
+          en.bt[d] += cs.BT[m][e][d];
+          en.b[d] += cs.B[m][e][d];
+        }
+      }
+    }
+    longest = std::max(longest, rows[q].size());
+  }
+  N.len = std::max(16, (int)(longest + 7) / 8 * 8);
+  N.ncol = ncol;
+  for (int c = 0; c < ncol; ++c) {
+    size_t m = 1;
+    for (int q = N.off[c]; q < N.off[c + 1]; ++q) m = std::max(m, rows[q].size());
+    N.clen[c] = std::max(16, (int)(m + 7) / 8 * 8);
+  }
+  const size_t sz = (size_t)N.len * nn;
+  std::vector<unsigned short> node(lv.L.vs, 0), cell;
+  std::vector<unsigned> col(sz / 2, 0);
+  auto set_col = [&](int e, int q, int r) { col[(size_t)(e / 2) * nn + q] |= (unsigned)r << (e & 1 ? 16 : 0); };
+  std::vector<double> A(sz, 0.0), BT(3 * sz, 0.0), B(3 * sz, 0.0), C(sz, 0.0), ainv(nn, 0.0), dinv(nn);
+  for (int q = 0; q < nn; ++q) {
+    for (int e = 0; e < N.len; ++e) {
+      const size_t at = (size_t)e * nn + q;
+      if (e >= (int)rows[q].size()) {
+        set_col(e, q, q);
+        continue;
+      }
+      const Entry& en = rows[q][e];
+      set_col(e, q, en.r);
+      A[at] = en.a;
+      C[at] = en.c;
+      for (int d = 0; d < 3; ++d) {
+        BT[d * sz + at] = en.bt[d];
+        B[d * sz + at] = en.b[d];
+      }
+      if (en.r == q && q < N.nfree) ainv[q] = 1.0 / en.a;
+    }
+    dinv[q] = H.dinv[own[q]];
+  }
+  for (long t = 0; t < (long)lv.L.ncell * lv.L.P; ++t) node[t] = (unsigned short)local[H.canon[t]];
+  std::vector<double> cellA(16 * (size_t)lv.L.ncell, 0.0);
+  for (int c = 0; c < lv.L.ncell; ++c)
+    for (int e = 0; e < kUPoints; ++e) cellA[16 * (size_t)c + e] = lv.hcs[c].A[0][e];
+  for (int q = N.off[lv.ncol_if]; q < N.off[ncol]; ++q) cell.push_back((unsigned short)occ[q][0].x);
+  N.ncell = lv.L.ncell;
+  N.cellA = upload(u, cellA);
+  N.cell = upload(u, cell);
+  N.work = upload(u, std::vector<double>(8 * (size_t)nn, 0.0));
+  N.col = upload(u, col);
+  N.A = upload(u, A);
+  N.BT = upload(u, BT);
+  N.B = upload(u, B);
+  N.C = upload(u, C);
+  N.ainv = upload(u, ainv);
+  N.dinv = upload(u, dinv);
+  N.own = upload(u, own);
+  N.node = upload(u, node);
+  N.n = nn;
+}
+
 }  // namespace
 
 UHier* u_build(const double* xyz, int nv, const int* tet, int nt, const std::vector<std::array<int, 3>>& outflow,
@@ -645,16 +756,10 @@ UHier* u_build(const double* xyz, int nv, const int* tet, int nt, const std::vec
     lv.lst.maxocc = 0;
     for (int q = 0; q < H.nlist; ++q) lv.lst.maxocc = std::max(lv.lst.maxocc, lv.h_off[q + 1] - lv.h_off[q]);
     lv.col_maxocc.assign(lv.col_off.size() > 0 ? lv.col_off.size() - 1 : 0, 0);
-    std::vector<int> col_sl(lv.col_maxocc.size(), 1);
-    for (size_t cc = 0; cc + 1 < lv.col_off.size(); ++cc) {
+    for (size_t cc = 0; cc + 1 < lv.col_off.size(); ++cc)
       for (int q = lv.col_off[cc]; q < lv.col_off[cc + 1]; ++q)
         lv.col_maxocc[cc] = std::max(lv.col_maxocc[cc], lv.h_off[q + 1] - lv.h_off[q]);
-      col_sl[cc] = if_slots(lv.col_maxocc[cc], lv.col_off[cc + 1] - lv.col_off[cc]);
-    }
-    if (!lv.col_off.empty()) {
-      lv.col_off_d = upload(*u, lv.col_off);
-      if (!col_sl.empty()) lv.col_sl_d = upload(*u, col_sl);
-    }
+    build_nodes(*u, lv, H);
     lv.dinv = upload(*u, H.dinv);
     lv.ml_own = upload(*u, H.mlown);
     lv.flags = upload(*u, H.flags);
