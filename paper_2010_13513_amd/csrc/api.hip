@@ -877,50 +877,57 @@ void op_smooth(hhg_hier h, int l, T* x, const T* b, int iters, int gs, int xi, d
                  lv.g.nn, 3);
   };
   const bool bf16_lv = std::is_same<T, float>::value && l - h->lmin < h->bf16_levels;
-  if (!lv.nu64 && !bf16_lv && gs_runs_supported(lv.g)) {
+  if (!bf16_lv && gs_runs_supported(lv.g)) {
     unsigned in_alt = 0;
     for (int it = 0; it < iters; ++it) {
       for (int s = 0; s < xi; ++s) {
         launch_gs_sweep<T>(S(h), lv.g, lconst<T>(lv), x, r, b, false, in_alt);
         if (gs == HHG_GS_SYM) launch_gs_sweep<T>(S(h), lv.g, lconst<T>(lv), x, r, b, true, in_alt);
       }
+      // Taylor-Hood pressure rows read velocities only (from the buffer that
+      // holds them) and do not depend on the viscosity: the constant-
+      // coefficient residual with the step in place
       PStep<T> ps;
       ps.p = x + 3 * (size_t)lv.g.vstride;
       ps.dinv = dinv<T>(lv);
       ps.omega = (T)omega;
-      launch_apply<T>(S(h), lv.g, lconst<T>(lv), tables<T>(lv), in_alt ? r : x, b, r, full_mask(h), true, false, true,
-                      lv.bnd, lv.nbnd, ps);
+      LevelConst<T> lc = lconst<T>(lv);
+      lc.nu = lc.ainv_site = nullptr;
+      launch_apply<T>(S(h), lv.g, lc, tables<T>(lv), in_alt ? r : x, b, r, full_mask(h), true, false, true, lv.bnd,
+                      lv.nbnd, ps);
     }
     if (in_alt) launch_scaled_copy<T>(S(h), x, r, nullptr, 3 * (size_t)lv.g.vstride, T(1));
     return;
   }
   for (int it = 0; it < iters; ++it) {
-    const bool whole = !lv.nu64 && !bf16_lv &&
+    const bool whole = !bf16_lv &&
                        launch_gs_level<T>(S(h), lv.g, lconst<T>(lv), x, b, xi, gs == HHG_GS_SYM);
     for (int s = 0; s < (whole ? 0 : xi); ++s) {
       for (int c = 0; c < ncol; ++c) colour(c);
       if (gs == HHG_GS_SYM)
         for (int c = ncol - 1; c >= 0; --c) colour(c);
     }
-    // r_p = g - B u + C p, then p -= omega D^{-1} r_p.  With constant
-    // coefficients the k-marching apply in its pressure-rows-only form (a
-    // few loads per lattice point, no velocity rows written).  Taylor-Hood
+    // r_p = g - B u + C p, then p -= omega D^{-1} r_p: the k-marching apply in
+    // its pressure-rows-only form (a few loads per lattice point, no velocity
+    // rows written).  Taylor-Hood
     // pressure rows read no p (C = 0): the step is applied in place by the
     // residual launch itself (no residual stored, one launch less per
     // iteration), except where the residual is rounded to bfloat16 first.
     const bool bf16_level = std::is_same<T, float>::value && l - h->lmin < h->bf16_levels;
-    if (!lv.nu64 && h->disc == HHG_P2P1 && !bf16_level) {
+    // The rows do not depend on the viscosity, so a variable one takes the
+    // same form.
+    LevelConst<T> lc = lconst<T>(lv);
+    if (!bf16_level) lc.nu = lc.ainv_site = nullptr;
+    if (h->disc == HHG_P2P1 && !bf16_level) {
       PStep<T> ps;
       ps.p = x + 3 * (size_t)lv.g.vstride;
       ps.dinv = dinv<T>(lv);
       ps.omega = (T)omega;
-      launch_apply<T>(S(h), lv.g, lconst<T>(lv), tables<T>(lv), x, b, r, full_mask(h), true, false, true, lv.bnd,
-                      lv.nbnd, ps);
+      launch_apply<T>(S(h), lv.g, lc, tables<T>(lv), x, b, r, full_mask(h), true, false, true, lv.bnd, lv.nbnd, ps);
     } else {
-      if (!lv.nu64)
-        op_apply<T>(h, l, full_mask(h), x, b, r, true, false, true);
-      else
-        op_apply<T>(h, l, full_mask(h) & 12, x, b, r, true, false, true);
+      launch_apply<T>(S(h), lv.g, lc, tables<T>(lv), x, b, r, lc.nu ? full_mask(h) & 12 : full_mask(h), true, false,
+                      true, lv.bnd, lv.nbnd);
+      round_out<T>(h, l, r, 0, 0, lv.vec_words, 1);
       launch_pressure_step<T>(S(h), lv.g, dinv<T>(lv), x, r, (T)omega);
     }
     round_out<T>(h, l, x, 0, 3 * (size_t)lv.g.vstride, lv.g.nn, 1);
@@ -1165,9 +1172,10 @@ void vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_para
     sc.nunk = h->nunk;
     sc.lds_words = (std::is_same<T, double>::value ? h->lds_end64 : h->lds_end32)[l - h->lmin];
     sc.q16 = std::is_same<T, float>::value ? h->bf16_levels : 0;
-    bool var = false;
-    for (int q = h->lmin; q <= l; ++q) var = var || h->L(q).nu64;
-    if (!launch_cycle_small<T>(S(h), slv<T>(h), sc, h->L(l).g.N, var)) launch_vcycle_small<T>(S(h), slv<T>(h), sc);
+    int with = 0;  // levels above the coarsest with a viscosity
+    for (int q = h->lmin + 1; q <= l; ++q) with += h->L(q).nu64 != nullptr;
+    const int nu = with == 0 ? 0 : (with == l - h->lmin ? 1 : 2);
+    if (!launch_cycle_small<T>(S(h), slv<T>(h), sc, h->L(l).g.N, nu)) launch_vcycle_small<T>(S(h), slv<T>(h), sc);
     return;
   }
   Level& lv = h->L(l);

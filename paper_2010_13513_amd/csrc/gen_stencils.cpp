@@ -603,7 +603,7 @@ void emit_sequence(FILE* f, const ElementSet& es, int G, const std::string& name
   };
   auto group = [&](int c) { return c < 2 ? 0 : c - 1; };
   std::vector<Box> need(G), step(seq.size());
-  Box pb, all;
+  Box pb, nb, all;
   const int z[3] = {0, 0, 0}, one[3] = {1, 1, 1};
   std::vector<int> wr(G, 0);
   for (int c : seq) {
@@ -622,12 +622,19 @@ void emit_sequence(FILE* f, const ElementSet& es, int G, const std::string& name
     };
     for (auto& e : pruned(es, 'A', g, 1)) around(e, need[e.g]);
     for (auto& e : pruned(es, 'T', g, 3)) around(e, pb);
+    for (auto& er : element_rows(es, g))  // vertex viscosities of the row's elements
+      for (int v = 0; v < 4; ++v) {
+        Entry e{};
+        e.di = er.vo[v][0], e.dj = er.vo[v][1], e.dk = er.vo[v][2];
+        around(e, nb);
+      }
   }
   for (int g = 0; g < G; ++g)
     if (wr[g]) need[g].add(z, one);  // the upper boundary layer of the last tile is copied with it
   for (int g = 0; g < G; ++g)
     if (need[g].any) all.add(need[g].lo, need[g].hi);
   all.add(pb.lo, pb.hi);
+  all.add(nb.lo, nb.hi);
   auto arr = [&](const int* v) {
     return "{" + std::to_string(v[0]) + ", " + std::to_string(v[1]) + ", " + std::to_string(v[2]) + "}";
   };

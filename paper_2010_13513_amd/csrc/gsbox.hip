@@ -21,12 +21,13 @@ namespace {
 // Bound by latency on these sizes: a launch, the box's loads in one batch and
 // a barrier and an LDS round trip per colour (Taylor-Hood, N = 16: 5 - 7 us
 // per run of four or five colours against 3.3 us per colour launch).
-template <typename Q, int TX, int TY, int TZ, int NT>
+template <typename Q, int TX, int TY, int TZ, int NT, bool VAR>
 struct BoxShape {
   static constexpr int BX = TX + Q::bhi[0] - Q::blo[0], BY = TY + Q::bhi[1] - Q::blo[1],
                        BZ = TZ + Q::bhi[2] - Q::blo[2];
   static constexpr int S1 = BX, S2 = BX * BY, SG = BX * BY * BZ;
-  static constexpr int words = SG * (Q::G + 1);
+  static constexpr int arrays = Q::G + (VAR ? 2 : 1);  // velocity groups, pressure, viscosity
+  static constexpr int words = SG * arrays;
   static constexpr int loads = (SG + NT - 1) / NT;
   // step s: box of updated sites; the vertex colours take every other i
   static constexpr int grp(int s) { return Q::col[s] < kGsVertexColours ? 0 : Q::col[s] - kGsVertexColours + 1; }
@@ -59,10 +60,10 @@ __device__ __forceinline__ void tile_of(const TileGrid& tg, int& tx, int& ty, in
   tz |= r << cz;
 }
 
-template <typename T, typename Q, int TX, int TY, int TZ, int NT>
+template <typename T, typename Q, int TX, int TY, int TZ, int NT, bool VAR>
 __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T* x, const T* alt, T* xw, T* altw,
                                                const T* __restrict__ b, unsigned in_alt, TileGrid tg) {
-  using Sh = BoxShape<Q, TX, TY, TZ, NT>;
+  using Sh = BoxShape<Q, TX, TY, TZ, NT, VAR>;
   using R = BoxRows<Q::G>;
   constexpr int G = Q::G, S1 = Sh::S1, S2 = Sh::S2, SG = Sh::SG;
   __shared__ T box[Sh::words];
@@ -73,7 +74,7 @@ __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T
   x0 *= TX, y0 *= TY, z0 *= TZ;
   const size_t dv = (size_t)d * g.vstride;
   const T* __restrict__ pv = x + 3 * (size_t)g.vstride;
-  T v[Sh::loads][G + 1];
+  T v[Sh::loads][Sh::arrays];
 #pragma unroll
   for (int q = 0; q < Sh::loads; ++q) {
     const int c = tid + q * NT;
@@ -84,10 +85,11 @@ __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T
 #pragma unroll
     for (int gr = 0; gr < G; ++gr) v[q][gr] = (((in_alt >> gr) & 1u) ? alt : x)[dv + gr * nn + at];
     v[q][G] = pv[at];
+    if constexpr (VAR) v[q][G + 1] = lc.nu[at];
   }
   // the sites this thread updates: box position (-1: none) and f
   int lp[Sh::total];
-  T f[Sh::total];
+  T f[Sh::total], ai[VAR ? Sh::total : 1];
   auto each = [&](auto&& fn) {
     auto go = [&](auto self, auto sc) {
       constexpr int s = decltype(sc)::value;
@@ -111,7 +113,9 @@ __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T
       const bool on = dd < Sh::D(s) && bx < TX + Q::hi[s][0] - Q::blo[0] && vel_interior<G>(gr, i, j, k, N);
       lp[Sh::first(s) + q] =
           on ? bx + S1 * (Q::lo[s][1] - Q::blo[1] + h) + S2 * (Q::lo[s][2] - Q::blo[2] + dd) : -1;
-      f[Sh::first(s) + q] = on ? b[dv + (gr * nn + i + n1 * j + n2 * k)] : T(0);
+      const int at = gr * nn + i + n1 * j + n2 * k;
+      f[Sh::first(s) + q] = on ? b[dv + at] : T(0);
+      if constexpr (VAR) ai[Sh::first(s) + q] = on ? lc.ainv_site[at] : T(0);
     }
   });
 #pragma unroll
@@ -119,7 +123,7 @@ __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T
     const int c = tid + q * NT;
     if (c < SG) {
 #pragma unroll
-      for (int gr = 0; gr <= G; ++gr) box[gr * SG + c] = v[q][gr];
+      for (int gr = 0; gr < Sh::arrays; ++gr) box[gr * SG + c] = v[q][gr];
     }
   }
   __syncthreads();
@@ -134,12 +138,17 @@ __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T
   });
   each([&](auto sc) {
     constexpr int s = decltype(sc)::value, gr = Sh::grp(s);
-    const T ai = lc.ainv[gr];
 #pragma unroll
     for (int q = 0; q < Sh::passes(s); ++q) {
       const int l = lp[Sh::first(s) + q];
-      if (l >= 0)
-        box[gr * SG + l] += (f[Sh::first(s) + q] - sa * R::template A<T, gr, S1, S2, SG>(box + gr * SG + l)) * ai;
+      if (l >= 0) {
+        T* u = box + gr * SG + l;
+        if constexpr (VAR)
+          *u += (f[Sh::first(s) + q] - lc.a * R::template Anu<T, gr, S1, S2, SG>(u, box + (G + 1) * SG + l)) *
+                ai[Sh::first(s) + q];
+        else
+          *u += (f[Sh::first(s) + q] - sa * R::template A<T, gr, S1, S2, SG>(u)) * lc.ainv[gr];
+      }
     }
     __syncthreads();
   });
@@ -168,17 +177,19 @@ __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T
 // launch apart.  Bound by the chain of colours: Taylor-Hood, N = 8, three
 // sweeps: 27 launches of 3.2 us before, 20.6 us in one launch now (0.6 us per
 // colour); P1, N = 16, three sweeps: 6 x 3.1 -> 12.6 us.
-template <typename T, int G, int N, int NT>
+template <typename T, int G, int N, int NT, bool VAR>
 __global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict__ x, const T* __restrict__ b, int xi,
                                                  int sym) {
   using R = BoxRows<G>;
   constexpr int S1 = N + 1, S2 = S1 * S1, nn = S2 * S1, VS = G * nn, NC = gs_colours(G);
-  __shared__ T box[VS + nn];
+  __shared__ T box[VS + nn + (VAR ? nn : 0)];
   const int tid = threadIdx.x, d = blockIdx.x;
   T* __restrict__ xd = x + d * VS;
   const T* __restrict__ bd = b + d * VS;
   for (int c = tid; c < VS; c += NT) box[c] = xd[c];
   for (int c = tid; c < nn; c += NT) box[VS + c] = x[3 * VS + c];
+  if constexpr (VAR)
+    for (int c = tid; c < nn; c += NT) box[VS + nn + c] = lc.nu[c];
   constexpr auto grp = [](int c) constexpr { return c < kGsVertexColours ? 0 : c - kGsVertexColours + 1; };
   constexpr auto dim = [](int c, int axis) constexpr {
     const int g = c < kGsVertexColours ? 0 : c - kGsVertexColours + 1;
@@ -195,7 +206,7 @@ __global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict
   constexpr int P = PV > PE ? PV : PE;
   static_assert(G == 1 || PE * NT >= N * N * (N - 1), "passes cover every edge group");
   int lp[NC][P];
-  T f[NC][P];
+  T f[NC][P], ai[VAR ? NC : 1][P];
   auto colours = [&](auto&& fn) {
     auto go = [&](auto self, auto cc) {
       constexpr int c = decltype(cc)::value;
@@ -220,6 +231,7 @@ __global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict
       const int l = g * nn + i + S1 * j + S2 * k;
       lp[c][q] = on ? l : -1;
       f[c][q] = on ? bd[l] : T(0);
+      if constexpr (VAR) ai[c][q] = on ? lc.ainv_site[l] : T(0);
     }
   });
   __syncthreads();
@@ -236,7 +248,10 @@ __global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict
     for (int q = 0; q < P; ++q)
       if (lp[c][q] >= 0) {
         T* u = box + lp[c][q];
-        *u += (f[c][q] - sa * R::template A<T, g, S1, S2, nn>(u)) * lc.ainv[g];
+        if constexpr (VAR)
+          *u += (f[c][q] - lc.a * R::template Anu<T, g, S1, S2, nn>(u, box + VS + nn + lp[c][q] - g * nn)) * ai[c][q];
+        else
+          *u += (f[c][q] - sa * R::template A<T, g, S1, S2, nn>(u)) * lc.ainv[g];
       }
     __syncthreads();
   };
@@ -251,8 +266,7 @@ __global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict
 
 }  // namespace
 
-// One Gauss-Seidel sweep of the Taylor-Hood velocity with constant
-// coefficients in runs of colours: x and alt hold the same vector, in_alt the
+// One Gauss-Seidel sweep of the Taylor-Hood velocity in runs of colours: x and alt hold the same vector, in_alt the
 // groups whose current values are in alt; every run flips the bits of its
 // groups, so a whole sweep flips all of them.
 template <typename T, typename Q, int TX, int TY, int TZ, int NT>
@@ -271,14 +285,21 @@ void launch_gs_run(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, 
   }
   KScope ks(s, KF_GS_EDGE, sites);
   const TileGrid tg{log2i(g.N / TX), log2i(g.N / TY), log2i(g.N / TZ)};
-  hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT>), dim3(3 << (tg.lx + tg.ly + tg.lz)), dim3(NT), 0, s, g, lc, x,
-                     alt, x, alt, b, in_alt, tg);
+  const dim3 grid(3 << (tg.lx + tg.ly + tg.lz));
+  if (lc.nu)
+    hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT, true>), grid, dim3(NT), 0, s, g, lc, x, alt, x, alt, b, in_alt,
+                       tg);
+  else
+    hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT, false>), grid, dim3(NT), 0, s, g, lc, x, alt, x, alt, b, in_alt,
+                       tg);
   for (int gr = 0; gr < Q::G; ++gr) in_alt ^= (unsigned)Q::wr[gr] << gr;
 }
 
 bool gs_runs_supported(const Geom& g) { return g.G == 8 && (g.N == 16 || g.N == 32) && g.nf == 0; }
 
-// Measured per Uzawa iteration with three forward sweeps (float64 / float32),
+// Variable viscosity takes the same runs (float32 V(3,3) with three sweeps to N =
+// 64: 4.29 -> 3.15 ms).  Measured per Uzawa iteration with three forward sweeps
+// (float64 / float32, constant coefficients),
 // against a launch per colour: N = 16 105 -> 49 / 100 -> 42 us with two runs
 // on 4^3 tiles (three runs: 53 / 48; 8 x 4 x 4 tiles: 57 / 48), N = 32 125 ->
 // 101 / 110 -> 77 us with three runs on 8^3 tiles (4^3 tiles: 130 / 102; 8 x 8
@@ -319,7 +340,10 @@ bool launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x
   if (g.G == G_ && g.N == N_) {                                                                                     \
     const double m = (G_ == 1 ? g.N : 2 * g.N) - 1;                                                                 \
     KScope ks(s, KF_GS_EDGE, m * m * m * xi * (sym ? 2 : 1));                                                       \
-    hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_>), dim3(3), dim3(NT_), 0, s, lc, x, b, xi, (int)sym);            \
+    if (lc.nu)                                                                                                      \
+      hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_, true>), dim3(3), dim3(NT_), 0, s, lc, x, b, xi, (int)sym);    \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_, false>), dim3(3), dim3(NT_), 0, s, lc, x, b, xi, (int)sym);   \
     return true;                                                                                                    \
   }
   HHG_LEVEL(8, 8, 512)

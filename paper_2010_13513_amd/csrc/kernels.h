@@ -168,9 +168,10 @@ constexpr int kSmallLdsBytes = 128 * 1024;
 template <typename T>
 void launch_vcycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc);
 // The same cycle by the kernel specialised on the top level's lattice size
-// (constant coefficients; false: not supported, nothing launched).
+// (nu: 0 constant coefficients, 1 a viscosity on every level above the
+// coarsest, 2 mixed; false: not supported, nothing launched).
 template <typename T>
-bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc, int ntop, bool var);
+bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc, int ntop, int nu);
 // Allow kSmallLdsBytes of dynamic LDS for the one-workgroup V-cycle kernels.
 void small_kernel_attributes();
 

@@ -54,23 +54,24 @@ struct Shape {
   // wavefronts per velocity component in the sweeps (every colour in one pass)
   static constexpr int waves = most() == 0 ? 1 : (most() + 63) / 64;
 };
-// LDS layout: the weight table, then [x | b] of every level from the top
-// down to N = 1, then one residual vector of the top level's size.
-template <int G, int NTOP>
+// LDS layout: the weight table, then [x | b] (and the vertex viscosities when
+// they vary) of every level from the top down to N = 1, then one residual
+// vector of the top level's size.
+template <int G, int NTOP, bool VAR>
 struct Layout {
   static constexpr int table = 27 * PRows<G>::n * PRows<G>::m;
   template <int N>
   static constexpr int xoff() {
     if constexpr (N >= NTOP) return table;
-    else return xoff<2 * N>() + 2 * Shape<G, 2 * N>::words;
+    else return xoff<2 * N>() + 2 * Shape<G, 2 * N>::words + (VAR ? Shape<G, 2 * N>::nn : 0);
   }
-  static constexpr int roff = xoff<1>() + 2 * Shape<G, 1>::words;
+  static constexpr int roff = xoff<1>() + 2 * Shape<G, 1>::words + (VAR ? Shape<G, 1>::nn : 0);
   static constexpr int words = roff + Shape<G, NTOP>::words;
 };
 
-template <typename T, int G, int NTOP, int NT>
+template <typename T, int G, int NTOP, int NT, bool VAR>
 struct Cycle {
-  using L = Layout<G, NTOP>;
+  using L = Layout<G, NTOP, VAR>;
   using R = BoxRows<G>;
   using PR = PRows<G>;
   static constexpr int NW = NT / 64;
@@ -84,7 +85,20 @@ struct Cycle {
   __device__ __forceinline__ T* X() const { return box + L::template xoff<N>(); }
   template <int N>
   __device__ __forceinline__ T* B() const { return box + L::template xoff<N>() + Shape<G, N>::words; }
+  template <int N>
+  __device__ __forceinline__ T* Nu() const { return box + L::template xoff<N>() + 2 * Shape<G, N>::words; }
   __device__ __forceinline__ T* Rv() const { return box + L::roff; }
+
+  // A's row of group g at velocity word l of component d; sa: unit of the
+  // integer weights (or, with a viscosity, of the element rows).
+  template <int N, int g>
+  __device__ __forceinline__ T arow(T sa, const T* x, int l, int d) const {
+    using S = Shape<G, N>;
+    if constexpr (VAR)
+      return sa * R::template Anu<T, g, S::S1, S::S2, S::nn>(x + l, Nu<N>() + l - d * S::VS - g * S::nn);
+    else
+      return sa * R::template A<T, g, S::S1, S::S2, S::nn>(x + l);
+  }
 
   // Slice s of the pressure row at node t: B's component s, or (P1, s = 3)
   // the C row; weights at h = 1, table [entry][slice][class] (lanes of
@@ -149,7 +163,7 @@ struct Cycle {
     T* x = X<N>();
     const T* b = B<N>();
     T* r = Rv();
-    const T sa = lc.a / T(R::denA), sb = lc.b / T(R::denT);
+    const T sa = VAR ? lc.a : lc.a / T(R::denA), sb = lc.b / T(R::denT);
     const int d = wave / W;
     const bool act = d < 3;
     const int ct = tid - d * (64 * W);
@@ -164,18 +178,23 @@ struct Cycle {
       go(go, std::integral_constant<int, 0>{});
     };
     int lp[S::NC];
-    T f[S::NC];
+    T f[S::NC], ai[S::NC];
     colours([&](auto cc) {
       constexpr int c = decltype(cc)::value, g = S::grp(c), M = S::count(c);
       constexpr bool half = c < kGsVertexColours;
       lp[c] = -1;
       f[c] = 0;
+      ai[c] = VAR ? T(0) : lc.ainv[g];
       if constexpr (M > 0) {
         constexpr int Wd = S::width(c), H = S::dim(g, 1);
         const int w = ct % Wd, rr = ct / Wd;
         const int j = 1 - gdir(G, g, 1) + rr % H, k = 1 - gdir(G, g, 2) + rr / H;
         const int i = half ? 1 + ((c + 1 + j + k) & 1) + 2 * w : 1 - gdir(G, g, 0) + w;
-        if (act && ct < M && i <= N - 1) lp[c] = d * S::VS + g * S::nn + i + S::S1 * j + S::S2 * k;
+        if (act && ct < M && i <= N - 1) {
+          const int at = g * S::nn + i + S::S1 * j + S::S2 * k;
+          lp[c] = d * S::VS + at;
+          if constexpr (VAR) ai[c] = lc.ainv_site[at];
+        }
       }
     });
     constexpr int PP = (S::nn + NT - 1) / NT;
@@ -200,16 +219,13 @@ struct Cycle {
         if (act)
           colours([&](auto cc) {
             constexpr int c = decltype(cc)::value, g = S::grp(c);
-            if (lp[c] >= 0) f[c] -= sa * R::template A<T, g, S::S1, S::S2, S::nn>(x + lp[c]);
+            if (lp[c] >= 0) f[c] -= arow<N, g>(sa, x, lp[c], d);
           });
       } else {
         auto relax = [&](auto cc) {
           constexpr int c = decltype(cc)::value, g = S::grp(c);
           if constexpr (S::count(c) > 0) {
-            if (lp[c] >= 0) {
-              T* u = x + lp[c];
-              *u += (f[c] - sa * R::template A<T, g, S::S1, S::S2, S::nn>(u)) * lc.ainv[g];
-            }
+            if (lp[c] >= 0) x[lp[c]] += (f[c] - arow<N, g>(sa, x, lp[c], d)) * ai[c];
             colour_sync<N>();
           }
         };
@@ -460,9 +476,9 @@ struct Cycle {
   }
 };
 
-template <typename T, int G, int NTOP, int NT>
+template <typename T, int G, int NTOP, int NT, bool VAR>
 __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restrict__ lv, SmallCycle<T> sc) {
-  using L = Layout<G, NTOP>;
+  using L = Layout<G, NTOP, VAR>;
   using S = Shape<G, NTOP>;
   constexpr int spare = G == 1 ? 4 * S::nn : 0;  // Cycle::scratch
   __shared__ T box[L::words + spare];
@@ -479,23 +495,37 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
     box[L::table + t] = sc.x[t];
     box[L::table + S::words + t] = sc.b[t];
   }
+  if constexpr (VAR) {  // every level's viscosity above the coarsest
+    auto load = [&](auto self, auto nc, int q) {
+      constexpr int N = decltype(nc)::value;
+      T* nu = box + L::template xoff<N>() + 2 * Shape<G, N>::words;
+      for (int t = tid; t < Shape<G, N>::nn; t += NT) nu[t] = lv[q].lc.nu[t];
+      if constexpr (N > 1)
+        if (q > 1) self(self, std::integral_constant<int, N / 2>{}, q - 1);
+    };
+    load(load, std::integral_constant<int, NTOP>{}, sc.nlev - 1);
+  }
   __syncthreads();
-  const Cycle<T, G, NTOP, NT> cy{lv, sc, box, red, tid, __builtin_amdgcn_readfirstlane(tid / 64), tid % 64};
+  const Cycle<T, G, NTOP, NT, VAR> cy{lv, sc, box, red, tid, __builtin_amdgcn_readfirstlane(tid / 64), tid % 64};
   cy.template run<NTOP>(sc.nlev - 1);
   for (int t = tid; t < S::words; t += NT) sc.x[t] = box[L::table + t];
 }
 
 }  // namespace
 
-// False (nothing launched) where the general kernel is needed: variable
-// viscosity, bfloat16 levels, other lattice sizes, more unknowns than threads.
+// False (nothing launched) where the general kernel is needed: bfloat16
+// levels, a viscosity on some of the levels only (nu: 0 none, 1 all above the
+// coarsest, 2 mixed), other lattice sizes, more unknowns than threads.
 template <typename T>
-bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc, int ntop, bool var) {
-  if (var || sc.q16 > 0 || sc.nlev < 2) return false;
+bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc, int ntop, int nu) {
+  if (nu > 1 || sc.q16 > 0 || sc.nlev < 2) return false;
 #define HHG_SMALL(G_, N_, NT_)                                                                  \
   if (sc.G == G_ && ntop == N_ && sc.nunk <= NT_) {                                             \
     KScope ks(s, KF_SMALL, sc.nlev);                                                            \
-    hipLaunchKernelGGL((k_cycle_small<T, G_, N_, NT_>), dim3(1), dim3(NT_), 0, s, lv, sc);     \
+    if (nu)                                                                                     \
+      hipLaunchKernelGGL((k_cycle_small<T, G_, N_, NT_, true>), dim3(1), dim3(NT_), 0, s, lv, sc); \
+    else                                                                                        \
+      hipLaunchKernelGGL((k_cycle_small<T, G_, N_, NT_, false>), dim3(1), dim3(NT_), 0, s, lv, sc); \
     return true;                                                                                \
   }
   HHG_SMALL(8, 4, 512)
@@ -505,7 +535,7 @@ bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle
 #undef HHG_SMALL
   return false;
 }
-template bool launch_cycle_small<double>(hipStream_t, const SmallLevel<double>*, const SmallCycle<double>&, int, bool);
-template bool launch_cycle_small<float>(hipStream_t, const SmallLevel<float>*, const SmallCycle<float>&, int, bool);
+template bool launch_cycle_small<double>(hipStream_t, const SmallLevel<double>*, const SmallCycle<double>&, int, int);
+template bool launch_cycle_small<float>(hipStream_t, const SmallLevel<float>*, const SmallCycle<float>&, int, int);
 
 }  // namespace hhg

@@ -1,15 +1,16 @@
 """Gauss-Seidel sweeps that run several colours per launch on boxes of the
 lattice in LDS (whole small levels, overlapped tiles on the middle levels):
 the smoother against the oracle's pointwise multicolour sweeps at every size
-with its own tiling, in both precisions, forward and symmetric, with an odd
-and an even number of sweeps (the tiles alternate between two buffers)."""
+with its own tiling, in both precisions, constant and variable viscosity, forward and
+symmetric, with an odd and an even number of sweeps (the tiles alternate
+between two buffers)."""
 import numpy as np
 import pytest
 
-from oracle import fe
+from oracle import fe, mesh
 from oracle.smoother import Uzawa
 from oracle.stokes import Stokes
-from paper_2010_13513_amd import hhg
+from paper_2010_13513_amd import hhg, workloads as W
 from tests.gpu_util import Lib, assert_blocks
 
 pytestmark = pytest.mark.gpu
@@ -18,21 +19,32 @@ P1, P2 = hhg.HHG_P1P1, hhg.HHG_P2P1
 _ORACLE = {}
 
 
-def _oracle(vorder, N):
-    if (vorder, N) not in _ORACLE:
-        _ORACLE[vorder, N] = Uzawa(Stokes(fe.Level(N, vorder)), "sd")
-    return _ORACLE[vorder, N]
+NU = W.gaussian_bump_viscosity(W.SEED_BASE + 4000, N_ref=32)
+
+
+def _nu(N):
+    c = mesh.p1_coords(N) / float(N)
+    return NU(c[:, 0], c[:, 1], c[:, 2])
+
+
+def _oracle(vorder, N, varnu):
+    if (vorder, N, varnu) not in _ORACLE:
+        _ORACLE[vorder, N, varnu] = Uzawa(Stokes(fe.Level(N, vorder, _nu(N) if varnu else None)), "sd")
+    return _ORACLE[vorder, N, varnu]
 
 
 @pytest.mark.parametrize("gs,xi,iters", [(hhg.HHG_GS_FWD, 3, 1), (hhg.HHG_GS_FWD, 1, 2), (hhg.HHG_GS_SYM, 1, 1)])
 @pytest.mark.parametrize("disc,L", [(P1, 3), (P1, 4), (P2, 2), (P2, 3), (P2, 4), (P2, 5)])
-def test_smooth_boxes(disc, L, gs, xi, iters):
+@pytest.mark.parametrize("varnu", [False, True])
+def test_smooth_boxes(disc, L, gs, xi, iters, varnu):
     vorder = 1 if disc == P1 else 2
-    U = _oracle(vorder, 2 ** L)
+    U = _oracle(vorder, 2 ** L, varnu)
     n = U.S.n
     rng = np.random.default_rng(13513 + 100 * L + vorder)
     lib = Lib(disc, L - 1, L)
     try:
+        if varnu:
+            hhg.hhg_set_viscosity(lib.h, L, lib.torch.from_numpy(_nu(2 ** L)).to(lib.dev))
         for prec, rnd, tol in ((hhg.HHG_F64, lambda a: a, 1e-12),
                                (hhg.HHG_F32, lambda a: a.astype(np.float32).astype(float), 500 * 2.0 ** -24)):
             x, b = rnd(rng.standard_normal(n)), rnd(rng.standard_normal(n))
