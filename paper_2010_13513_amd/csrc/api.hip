@@ -876,62 +876,57 @@ void op_smooth(hhg_hier h, int l, T* x, const T* b, int iters, int gs, int xi, d
     round_out<T>(h, l, x, lv.g.vstride, c < kGsVertexColours ? 0 : (size_t)(c - kGsVertexColours + 1) * lv.g.nn,
                  lv.g.nn, 3);
   };
-  const bool bf16_lv = std::is_same<T, float>::value && l - h->lmin < h->bf16_levels;
-  if (!bf16_lv && gs_runs_supported(lv.g)) {
-    unsigned in_alt = 0;
-    for (int it = 0; it < iters; ++it) {
-      for (int s = 0; s < xi; ++s) {
-        launch_gs_sweep<T>(S(h), lv.g, lconst<T>(lv), x, r, b, false, in_alt);
-        if (gs == HHG_GS_SYM) launch_gs_sweep<T>(S(h), lv.g, lconst<T>(lv), x, r, b, true, in_alt);
-      }
-      // Taylor-Hood pressure rows read velocities only (from the buffer that
-      // holds them) and do not depend on the viscosity: the constant-
-      // coefficient residual with the step in place
-      PStep<T> ps;
-      ps.p = x + 3 * (size_t)lv.g.vstride;
-      ps.dinv = dinv<T>(lv);
-      ps.omega = (T)omega;
-      LevelConst<T> lc = lconst<T>(lv);
-      lc.nu = lc.ainv_site = nullptr;
-      launch_apply<T>(S(h), lv.g, lc, tables<T>(lv), in_alt ? r : x, b, r, full_mask(h), true, false, true, lv.bnd,
-                      lv.nbnd, ps);
-    }
-    if (in_alt) launch_scaled_copy<T>(S(h), x, r, nullptr, 3 * (size_t)lv.g.vstride, T(1));
-    return;
-  }
+  // A level that holds bfloat16 values is rounded after every colour and step;
+  // the others take several colours per launch where the sizes allow: runs
+  // with the velocity (groups in_alt) alternating between x and the level's
+  // residual vector, or the whole level in one launch.  There the P1 pressure
+  // alternates too (p_alt), so that its step needs no launch of its own.
+  const bool sym = gs == HHG_GS_SYM;
+  const bool bf16_level = std::is_same<T, float>::value && l - h->lmin < h->bf16_levels;
+  const bool runs = !bf16_level && gs_runs_supported(lv.g, xi, sym);
+  const bool whole = !bf16_level && !runs && gs_level_supported(lv.g, xi, sym);
+  const bool fused = !bf16_level && (h->disc == HHG_P2P1 || runs || whole);
+  const size_t vs3 = 3 * (size_t)lv.g.vstride;
+  unsigned in_alt = 0;
+  bool p_alt = false;
   for (int it = 0; it < iters; ++it) {
-    const bool whole = !bf16_lv &&
-                       launch_gs_level<T>(S(h), lv.g, lconst<T>(lv), x, b, xi, gs == HHG_GS_SYM);
-    for (int s = 0; s < (whole ? 0 : xi); ++s) {
-      for (int c = 0; c < ncol; ++c) colour(c);
-      if (gs == HHG_GS_SYM)
-        for (int c = ncol - 1; c >= 0; --c) colour(c);
+    const T* p = (p_alt ? r : x) + vs3;
+    if (runs) {
+      launch_gs_runs<T>(S(h), lv.g, lconst<T>(lv), x, r, p, b, xi, sym, in_alt);
+    } else if (whole) {
+      launch_gs_level<T>(S(h), lv.g, lconst<T>(lv), x, p, b, xi, sym);
+    } else {
+      for (int s = 0; s < xi; ++s) {
+        for (int c = 0; c < ncol; ++c) colour(c);
+        if (sym)
+          for (int c = ncol - 1; c >= 0; --c) colour(c);
+      }
     }
     // r_p = g - B u + C p, then p -= omega D^{-1} r_p: the k-marching apply in
     // its pressure-rows-only form (a few loads per lattice point, no velocity
-    // rows written).  Taylor-Hood
-    // pressure rows read no p (C = 0): the step is applied in place by the
-    // residual launch itself (no residual stored, one launch less per
-    // iteration), except where the residual is rounded to bfloat16 first.
-    const bool bf16_level = std::is_same<T, float>::value && l - h->lmin < h->bf16_levels;
-    // The rows do not depend on the viscosity, so a variable one takes the
-    // same form.
-    LevelConst<T> lc = lconst<T>(lv);
-    if (!bf16_level) lc.nu = lc.ainv_site = nullptr;
-    if (h->disc == HHG_P2P1 && !bf16_level) {
-      PStep<T> ps;
-      ps.p = x + 3 * (size_t)lv.g.vstride;
-      ps.dinv = dinv<T>(lv);
-      ps.omega = (T)omega;
-      launch_apply<T>(S(h), lv.g, lc, tables<T>(lv), x, b, r, full_mask(h), true, false, true, lv.bnd, lv.nbnd, ps);
-    } else {
-      launch_apply<T>(S(h), lv.g, lc, tables<T>(lv), x, b, r, lc.nu ? full_mask(h) & 12 : full_mask(h), true, false,
-                      true, lv.bnd, lv.nbnd);
-      round_out<T>(h, l, r, 0, 0, lv.vec_words, 1);
+    // rows written).  The step is applied by that launch itself -- in place for
+    // Taylor-Hood, whose pressure rows read no p (C = 0) -- except where the
+    // residual is rounded to bfloat16 first or p has to stay in place.  The
+    // rows do not depend on the viscosity.
+    PStep<T> ps;
+    ps.dinv = dinv<T>(lv);
+    ps.omega = (T)omega;
+    if (fused) {
+      if (h->disc == HHG_P1P1) p_alt = !p_alt;
+      ps.p = p;
+      ps.pout = (p_alt ? r : x) + vs3;
+      launch_uzawa_pressure<T>(S(h), lv.g, lconst<T>(lv), in_alt ? r : x, b, r, lv.bnd, lv.nbnd, ps);
+    } else if (!bf16_level) {
+      launch_uzawa_pressure<T>(S(h), lv.g, lconst<T>(lv), x, b, r, lv.bnd, lv.nbnd, ps);  // r_p alone
       launch_pressure_step<T>(S(h), lv.g, dinv<T>(lv), x, r, (T)omega);
+    } else {
+      op_apply<T>(h, l, full_mask(h) & (lv.nu64 ? 12 : 15), x, b, r, true, false, true);
+      launch_pressure_step<T>(S(h), lv.g, dinv<T>(lv), x, r, (T)omega);
+      round_out<T>(h, l, x, 0, vs3, lv.g.nn, 1);
     }
-    round_out<T>(h, l, x, 0, 3 * (size_t)lv.g.vstride, lv.g.nn, 1);
   }
+  const size_t from = in_alt ? 0 : vs3, to = p_alt ? vs3 + lv.g.nn : vs3;
+  if (from < to) launch_scaled_copy<T>(S(h), x + from, r + from, nullptr, to - from, T(1));
 }
 
 // Zero pressure mean (int p = 0, Sec. 2), the normalisation of the pressure

@@ -62,7 +62,8 @@ __device__ __forceinline__ void tile_of(const TileGrid& tg, int& tx, int& ty, in
 
 template <typename T, typename Q, int TX, int TY, int TZ, int NT, bool VAR>
 __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T* x, const T* alt, T* xw, T* altw,
-                                               const T* __restrict__ b, unsigned in_alt, TileGrid tg) {
+                                               const T* __restrict__ pv, const T* __restrict__ b, unsigned in_alt,
+                                               TileGrid tg) {
   using Sh = BoxShape<Q, TX, TY, TZ, NT, VAR>;
   using R = BoxRows<Q::G>;
   constexpr int G = Q::G, S1 = Sh::S1, S2 = Sh::S2, SG = Sh::SG;
@@ -73,7 +74,6 @@ __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T
   tile_of(tg, x0, y0, z0, d);
   x0 *= TX, y0 *= TY, z0 *= TZ;
   const size_t dv = (size_t)d * g.vstride;
-  const T* __restrict__ pv = x + 3 * (size_t)g.vstride;
   T v[Sh::loads][Sh::arrays];
 #pragma unroll
   for (int q = 0; q < Sh::loads; ++q) {
@@ -178,8 +178,8 @@ __global__ void __launch_bounds__(NT) k_gs_box(Geom g, LevelConst<T> lc, const T
 // sweeps: 27 launches of 3.2 us before, 20.6 us in one launch now (0.6 us per
 // colour); P1, N = 16, three sweeps: 6 x 3.1 -> 12.6 us.
 template <typename T, int G, int N, int NT, bool VAR>
-__global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict__ x, const T* __restrict__ b, int xi,
-                                                 int sym) {
+__global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict__ x, const T* __restrict__ pv,
+                                                 const T* __restrict__ b, int xi, int sym) {
   using R = BoxRows<G>;
   constexpr int S1 = N + 1, S2 = S1 * S1, nn = S2 * S1, VS = G * nn, NC = gs_colours(G);
   __shared__ T box[VS + nn + (VAR ? nn : 0)];
@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict
   T* __restrict__ xd = x + d * VS;
   const T* __restrict__ bd = b + d * VS;
   for (int c = tid; c < VS; c += NT) box[c] = xd[c];
-  for (int c = tid; c < nn; c += NT) box[VS + c] = x[3 * VS + c];
+  for (int c = tid; c < nn; c += NT) box[VS + c] = pv[c];
   if constexpr (VAR)
     for (int c = tid; c < nn; c += NT) box[VS + nn + c] = lc.nu[c];
   constexpr auto grp = [](int c) constexpr { return c < kGsVertexColours ? 0 : c - kGsVertexColours + 1; };
@@ -266,100 +266,144 @@ __global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict
 
 }  // namespace
 
-// One Gauss-Seidel sweep of the Taylor-Hood velocity in runs of colours: x and alt hold the same vector, in_alt the
-// groups whose current values are in alt; every run flips the bits of its
-// groups, so a whole sweep flips all of them.
-template <typename T, typename Q, int TX, int TY, int TZ, int NT>
-void launch_gs_run(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* b, unsigned& in_alt) {
-  auto log2i = [](int v) {
-    int l = 0;
-    while ((1 << l) < v) ++l;
-    return l;
-  };
-  double sites = 0;  // updated sites (the timer's work units)
+// Sites that a run updates (the timer's work units).
+template <typename Q>
+double run_sites(const Geom& g) {
+  double sites = 0;
   for (int q = 0; q < Q::n; ++q) {
     const int gr = Q::col[q] < kGsVertexColours ? 0 : Q::col[q] - kGsVertexColours + 1;
     double n = Q::col[q] < kGsVertexColours ? 0.5 : 1.0;
     for (int a = 0; a < 3; ++a) n *= g.N - 1 + gdir(Q::G, gr, a);
     sites += n;
   }
-  KScope ks(s, KF_GS_EDGE, sites);
+  return sites;
+}
+
+// One run of colours, from the buffers that hold their groups to the others.
+template <typename T, typename Q, int TX, int TY, int TZ, int NT>
+void launch_gs_run(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* p, const T* b,
+                   unsigned& in_alt) {
+  auto log2i = [](int v) {
+    int l = 0;
+    while ((1 << l) < v) ++l;
+    return l;
+  };
+  KScope ks(s, Q::G == 1 ? KF_GS_VERTEX : KF_GS_EDGE, run_sites<Q>(g));
   const TileGrid tg{log2i(g.N / TX), log2i(g.N / TY), log2i(g.N / TZ)};
   const dim3 grid(3 << (tg.lx + tg.ly + tg.lz));
   if (lc.nu)
-    hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT, true>), grid, dim3(NT), 0, s, g, lc, x, alt, x, alt, b, in_alt,
-                       tg);
+    hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT, true>), grid, dim3(NT), 0, s, g, lc, x, alt, x, alt, p, b,
+                       in_alt, tg);
   else
-    hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT, false>), grid, dim3(NT), 0, s, g, lc, x, alt, x, alt, b, in_alt,
-                       tg);
+    hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT, false>), grid, dim3(NT), 0, s, g, lc, x, alt, x, alt, p, b,
+                       in_alt, tg);
   for (int gr = 0; gr < Q::G; ++gr) in_alt ^= (unsigned)Q::wr[gr] << gr;
 }
 
-bool gs_runs_supported(const Geom& g) { return g.G == 8 && (g.N == 16 || g.N == 32) && g.nf == 0; }
+bool gs_runs_supported(const Geom& g, int xi, bool sym) {
+  if (g.nf != 0) return false;
+  return g.G == 8 ? g.N == 16 || g.N == 32 : g.N == 32 || (g.N == 64 && xi * (sym ? 2 : 1) > 1) || g.N > 64;
+}
 
-// Variable viscosity takes the same runs (float32 V(3,3) with three sweeps to N =
-// 64: 4.29 -> 3.15 ms).  Measured per Uzawa iteration with three forward sweeps
-// (float64 / float32, constant coefficients),
-// against a launch per colour: N = 16 105 -> 49 / 100 -> 42 us with two runs
-// on 4^3 tiles (three runs: 53 / 48; 8 x 4 x 4 tiles: 57 / 48), N = 32 125 ->
-// 101 / 110 -> 77 us with three runs on 8^3 tiles (4^3 tiles: 130 / 102; 8 x 8
-// x 4: 117 / 79).  From N = 64 on the layers recomputed around the tiles cost
-// what the saved passes over memory give (three runs on 8^3 tiles 524 us, a
-// launch per colour 410 us), so a colour stays a launch there.
+// Taylor-Hood.  Variable viscosity takes the same runs (float32 V(3,3) with three
+// sweeps to N = 64: 4.29 -> 3.15 ms).  Measured per Uzawa iteration with three
+// forward sweeps (float64 / float32, constant coefficients), against a launch
+// per colour: N = 16 105 -> 49 / 100 -> 42 us with two runs on 4^3 tiles (three
+// runs: 53 / 48; 8 x 4 x 4 tiles: 57 / 48), N = 32 125 -> 101 / 110 -> 77 us with
+// three runs on 8^3 tiles (4^3 tiles: 130 / 102; 8 x 8 x 4: 117 / 79).  From N =
+// 64 on the layers recomputed around the tiles cost what the saved passes over
+// memory give (three runs on 8^3 tiles 524 us, a launch per colour 410 us), so
+// a colour stays a launch there.
+// P1: the colours of the sweeps alternate, a colour next to itself (the turn of
+// a symmetric sweep) being idempotent; they are cut into runs of nearly equal
+// length.  Smoothing calls with three sweeps, a launch per colour -> now, us
+// (float64 / float32): N = 32 28.0 -> 20.6 / 24.5 -> 17.8 (8^3 tiles, runs of
+// three; of two 22.6 / 20.2), N = 64 53.7 -> 49.6 / 45.7 -> 36.4, N = 128 302 ->
+// 246 / 200 -> 170, N = 256 2842 -> 2406 / 1836 -> 1384 (16 x 8 x 8 tiles;
+// 8^3: 264 / 200 at N = 128).  Runs of four are better where a tile is 4-byte
+// words (N = 64 39.7, N = 256 1489 with two) and not with 8 (one workgroup per
+// CU then; N = 256 2427).  One forward sweep at N = 64 is two launches either
+// way with the copy back (28.1 against 28.6): a launch per colour there.
 template <typename T>
-void launch_gs_sweep(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* b, bool backward,
-                     unsigned& in_alt) {
-#define HHG_RUN(Q, ...) launch_gs_run<T, gen::Q, __VA_ARGS__>(s, g, lc, x, alt, b, in_alt)
-  if (g.N == 16) {
-    if (!backward) {
-      HHG_RUN(P2Fwd03, 4, 4, 4, 512);
-      HHG_RUN(P2Fwd48, 4, 4, 4, 512);
-    } else {
-      HHG_RUN(P2Bwd84, 4, 4, 4, 512);
-      HHG_RUN(P2Bwd30, 4, 4, 4, 512);
+void launch_gs_runs(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* p, const T* b,
+                    int xi, bool sym, unsigned& in_alt) {
+#define HHG_RUN(Q, ...) launch_gs_run<T, gen::Q, __VA_ARGS__>(s, g, lc, x, alt, p, b, in_alt)
+  if (g.G == 1) {
+    const int total = sym ? 2 * xi + 1 : 2 * xi, most = g.N == 32 ? 3 : (sizeof(T) == 4 ? 4 : 2);
+    const int runs = (total + most - 1) / most;
+    for (int done = 0, r = 0; r < runs; ++r) {
+      const int len = (total - done + runs - r - 1) / (runs - r);
+#define HHG_P1(S_, L_)                                                                        \
+  if ((done & 1) == S_ && len == L_) {                                                        \
+    if (g.N == 32) {                                                                          \
+      if constexpr (L_ <= 3) HHG_RUN(P1Seq##S_##L_, 8, 8, 8, 512);                            \
+    } else {                                                                                  \
+      if constexpr (L_ <= 2 || sizeof(T) == 4) HHG_RUN(P1Seq##S_##L_, 16, 8, 8, 512);         \
+    }                                                                                         \
+  }
+      HHG_P1(0, 1) HHG_P1(0, 2) HHG_P1(0, 3) HHG_P1(0, 4)
+      HHG_P1(1, 1) HHG_P1(1, 2) HHG_P1(1, 3) HHG_P1(1, 4)
+#undef HHG_P1
+      done += len;
     }
-  } else {
-    if (!backward) {
-      HHG_RUN(P2Fwd01, 8, 8, 8, 1024);
-      HHG_RUN(P2Fwd24, 8, 8, 8, 1024);
-      HHG_RUN(P2Fwd58, 8, 8, 8, 1024);
+    return;
+  }
+  for (int sw = 0; sw < xi * (sym ? 2 : 1); ++sw) {
+    const bool backward = sym && (sw & 1);
+    if (g.N == 16) {
+      if (!backward) {
+        HHG_RUN(P2Fwd03, 4, 4, 4, 512);
+        HHG_RUN(P2Fwd48, 4, 4, 4, 512);
+      } else {
+        HHG_RUN(P2Bwd84, 4, 4, 4, 512);
+        HHG_RUN(P2Bwd30, 4, 4, 4, 512);
+      }
     } else {
-      HHG_RUN(P2Bwd85, 8, 8, 8, 1024);
-      HHG_RUN(P2Bwd42, 8, 8, 8, 1024);
-      HHG_RUN(P2Bwd10, 8, 8, 8, 1024);
+      if (!backward) {
+        HHG_RUN(P2Fwd01, 8, 8, 8, 1024);
+        HHG_RUN(P2Fwd24, 8, 8, 8, 1024);
+        HHG_RUN(P2Fwd58, 8, 8, 8, 1024);
+      } else {
+        HHG_RUN(P2Bwd85, 8, 8, 8, 1024);
+        HHG_RUN(P2Bwd42, 8, 8, 8, 1024);
+        HHG_RUN(P2Bwd10, 8, 8, 8, 1024);
+      }
     }
   }
 #undef HHG_RUN
 }
 
-// The xi sweeps of one Uzawa iteration in place, one launch (levels that fit).
-template <typename T>
-bool launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* b, int xi, bool sym) {
+// Taylor-Hood N <= 8 and P1 N <= 16; P1 N = 16 with one sweep of two colours
+// costs less as two launches than the load and write-back around it (smoothing
+// call 14.6 against 17.6 us; two sweeps 21.5 against 15.6 us).
+bool gs_level_supported(const Geom& g, int xi, bool sym) {
   if (g.nf != 0) return false;
+  return g.G == 8 ? g.N == 4 || g.N == 8 : g.N == 8 || (g.N == 16 && xi * (sym ? 2 : 1) > 1);
+}
+template <typename T>
+void launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* p, const T* b, int xi,
+                     bool sym) {
+  const double m = (g.G == 1 ? g.N : 2 * g.N) - 1;
+  KScope ks(s, KF_GS_EDGE, m * m * m * xi * (sym ? 2 : 1));
 #define HHG_LEVEL(G_, N_, NT_)                                                                                      \
   if (g.G == G_ && g.N == N_) {                                                                                     \
-    const double m = (G_ == 1 ? g.N : 2 * g.N) - 1;                                                                 \
-    KScope ks(s, KF_GS_EDGE, m * m * m * xi * (sym ? 2 : 1));                                                       \
     if (lc.nu)                                                                                                      \
-      hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_, true>), dim3(3), dim3(NT_), 0, s, lc, x, b, xi, (int)sym);    \
+      hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_, true>), dim3(3), dim3(NT_), 0, s, lc, x, p, b, xi, (int)sym); \
     else                                                                                                            \
-      hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_, false>), dim3(3), dim3(NT_), 0, s, lc, x, b, xi, (int)sym);   \
-    return true;                                                                                                    \
+      hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_, false>), dim3(3), dim3(NT_), 0, s, lc, x, p, b, xi, (int)sym); \
   }
   HHG_LEVEL(8, 8, 512)
   HHG_LEVEL(8, 4, 128)
   HHG_LEVEL(1, 8, 192)
-  // one sweep of two colours costs less as two launches than the load and
-  // write-back around it (smoothing call 14.6 against 17.6 us; two sweeps
-  // 21.5 against 15.6 us)
-  if (xi * (sym ? 2 : 1) > 1) HHG_LEVEL(1, 16, 1024)
+  HHG_LEVEL(1, 16, 1024)
 #undef HHG_LEVEL
-  return false;
 }
 
-#define HHG_INSTANTIATE(T) \
-  template bool launch_gs_level<T>(hipStream_t, const Geom&, const LevelConst<T>&, T*, const T*, int, bool); \
-  template void launch_gs_sweep<T>(hipStream_t, const Geom&, const LevelConst<T>&, T*, T*, const T*, bool, unsigned&);
+#define HHG_INSTANTIATE(T)                                                                                          \
+  template void launch_gs_level<T>(hipStream_t, const Geom&, const LevelConst<T>&, T*, const T*, const T*, int,    \
+                                   bool);                                                                           \
+  template void launch_gs_runs<T>(hipStream_t, const Geom&, const LevelConst<T>&, T*, T*, const T*, const T*, int,  \
+                                  bool, unsigned&);
 
 HHG_INSTANTIATE(double)
 HHG_INSTANTIATE(float)

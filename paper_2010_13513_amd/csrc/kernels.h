@@ -175,14 +175,14 @@ bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle
 // Allow kSmallLdsBytes of dynamic LDS for the one-workgroup V-cycle kernels.
 void small_kernel_attributes();
 
-// Uzawa pressure step fused into the pressure rows of a residual launch:
-// with p set, a pressure row's residual r_k is not stored but applied as
-// p_k -= omega dinv_k r_k (eq. uzawa-pressure).  Only for operators whose
-// pressure rows do not read p (no C block: Taylor-Hood), so that the update
-// in place races with no read.
+// Uzawa pressure step fused into the pressure rows of a residual launch: with
+// p set, a pressure row's residual r_k is not stored but applied as pout_k =
+// p_k - omega dinv_k r_k (eq. uzawa-pressure).  pout is p itself where the
+// rows do not read p (no C block: Taylor-Hood), another buffer otherwise.
 template <typename T>
 struct PStep {
-  T* p = nullptr;
+  const T* p = nullptr;
+  T* pout = nullptr;
   const T* dinv = nullptr;
   T omega = T(0);
 };
@@ -190,16 +190,28 @@ struct PStep {
 // Launchers (kernels.hip).  All asynchronous on `s`.
 template <typename T>
 void launch_apply(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const Tables<T>* tb, const T* x, const T* b,
-                  T* y, int opmask, bool has_b, bool vel_rows, bool p_rows, const int* bnd, int nbnd,
-                  const PStep<T>& ps = PStep<T>{});
+                  T* y, int opmask, bool has_b, bool vel_rows, bool p_rows, const int* bnd, int nbnd);
+// The Uzawa pressure step of eq. uzawa-pressure on the whole level (constant
+// or variable coefficients: its rows do not depend on the viscosity): the
+// velocities of x, the pressures of ps.p, the right-hand side of b; ps.p null:
+// the residual alone, into the pressure part of r.
+template <typename T>
+void launch_uzawa_pressure(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const T* x, const T* b, T* r,
+                           const int* bnd, int nbnd, const PStep<T>& ps);
 template <typename T>
 void launch_gs_colour(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* b, int colour);
-bool gs_runs_supported(const Geom& g);
+// Several colours per launch (gsbox.hip).  Runs: the sweeps of one Uzawa
+// iteration with the velocity groups alternating between x and alt (bit g of
+// in_alt: group g is in alt; all bits equal between calls).  Level: the same
+// in place, one launch.  p: the pressures.
+bool gs_runs_supported(const Geom& g, int xi, bool sym);
+bool gs_level_supported(const Geom& g, int xi, bool sym);
 template <typename T>
-bool launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* b, int xi, bool sym);
+void launch_gs_runs(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* p, const T* b,
+                    int xi, bool sym, unsigned& in_alt);
 template <typename T>
-void launch_gs_sweep(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* b, bool backward,
-                     unsigned& in_alt);
+void launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* p, const T* b, int xi,
+                     bool sym);
 template <typename T>
 void launch_pressure_step(hipStream_t s, const Geom& g, const T* dinv, T* x, const T* rp, T omega);
 template <typename T>

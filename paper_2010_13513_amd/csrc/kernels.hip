@@ -165,8 +165,7 @@ __device__ __forceinline__ int xcd_block_of(int nmain) {
 template <typename T, int G>
 __device__ __forceinline__ void prow_bnd_block(const Geom& g, const LevelConst<T>& lc, const T* __restrict__ x,
                                                const T* __restrict__ b, T* __restrict__ y, int opmask, int has_b,
-                                               const int* __restrict__ bnd, int nbnd, int nmain, int bs,
-                                               PStep<T> ps);
+                                               const int* __restrict__ bnd, int nbnd, int nmain, int bs);
 
 // Pressure row value at any node t = (i, j, k): interior rows from the
 // generated interior stencils, boundary rows from the generated per-class
@@ -283,7 +282,7 @@ __global__ void __launch_bounds__(kBlock) k_apply(Geom g, LevelConst<T> lc, cons
                                                   int vel_rows, int p_rows, const int* __restrict__ bnd, int nbnd,
                                                   int nmain) {
   if ((int)blockIdx.x >= nmain) {
-    prow_bnd_block<T, G>(g, lc, x, b, y, opmask, has_b, bnd, nbnd, nmain, kBlock, PStep<T>{});
+    prow_bnd_block<T, G>(g, lc, x, b, y, opmask, has_b, bnd, nbnd, nmain, kBlock);
     return;
   }
   const int t = xcd_block_of(nmain) * kBlock + threadIdx.x;
@@ -352,8 +351,9 @@ struct ZmCol {
 
 template <typename T, int G, int D, int Q, bool VEL, bool HB>
 __device__ __forceinline__ void zm_step(const Geom& g, const LevelConst<T>& lc, const T* __restrict__ x,
-                                        const T* __restrict__ b, T* __restrict__ y, const ZmCol<T>& c, int q,
-                                        T (&acc)[3][G + 1], T (*pshare)[3][kZmCols], const PStep<T>& ps) {
+                                        const T* __restrict__ px, const T* __restrict__ b, T* __restrict__ y,
+                                        const ZmCol<T>& c, int q, T (&acc)[3][G + 1], T (*pshare)[3][kZmCols],
+                                        const PStep<T>& ps) {
   constexpr int S = (Q + 2) % 3;  // slot of the row plane completed by this step
   const int N = g.N, s1 = g.n1, s2 = g.n1 * g.n1, nn = g.nn, vs = g.vstride;
   const int kp = c.k0 - 1 + q;
@@ -362,7 +362,7 @@ __device__ __forceinline__ void zm_step(const Geom& g, const LevelConst<T>& lc, 
   const int vo[3] = {(c.nb[0] + kps) * (int)sizeof(T), (c.nb[1] + kps) * (int)sizeof(T),
                      (c.nb[2] + kps) * (int)sizeof(T)};
   const __amdgpu_buffer_rsrc_t ru = gen::make_rsrc(x + (size_t)D * vs, (unsigned)((size_t)vs * sizeof(T)));
-  const __amdgpu_buffer_rsrc_t rp = gen::make_rsrc(x + (size_t)3 * vs, (unsigned)((size_t)nn * sizeof(T)));
+  const __amdgpu_buffer_rsrc_t rp = gen::make_rsrc(px, (unsigned)((size_t)nn * sizeof(T)));
   // residual: the b words of the row this step completes are loaded before
   // the plane's multiply-adds, so their latency hides behind them instead of
   // adding a round trip before the stores (address clamped into the lattice;
@@ -398,7 +398,7 @@ __device__ __forceinline__ void zm_step(const Geom& g, const LevelConst<T>& lc, 
       const int pp = 3 * vs + at;
       const T r = HB ? bv[G] - v : v;
       if (HB && !VEL && ps.p)
-        ps.p[at] -= ps.omega * ps.dinv[at] * r;
+        ps.pout[at] = ps.p[at] - ps.omega * ps.dinv[at] * r;
       else
         y[pp] = r;
     }
@@ -409,8 +409,8 @@ __device__ __forceinline__ void zm_step(const Geom& g, const LevelConst<T>& lc, 
 
 template <typename T, int G, int D, bool VEL, bool HB>
 __device__ __forceinline__ void zm_run(const Geom& g, const LevelConst<T>& lc, const T* __restrict__ x,
-                                       const T* __restrict__ b, T* __restrict__ y, const ZmCol<T>& c,
-                                       T (*pshare)[3][kZmCols], const PStep<T>& ps) {
+                                       const T* __restrict__ px, const T* __restrict__ b, T* __restrict__ y,
+                                       const ZmCol<T>& c, T (*pshare)[3][kZmCols], const PStep<T>& ps) {
   T acc[3][G + 1];
 #pragma unroll
   for (int s = 0; s < 3; ++s)
@@ -418,26 +418,27 @@ __device__ __forceinline__ void zm_run(const Geom& g, const LevelConst<T>& lc, c
     for (int r = 0; r <= G; ++r) acc[s][r] = T(0);
   const int nq = c.k1 - c.k0 + 2;
   for (int q = 0; q < nq; q += 3) {
-    zm_step<T, G, D, 0, VEL, HB>(g, lc, x, b, y, c, q, acc, pshare, ps);
-    if (q + 1 < nq) zm_step<T, G, D, 1, VEL, HB>(g, lc, x, b, y, c, q + 1, acc, pshare, ps);
-    if (q + 2 < nq) zm_step<T, G, D, 2, VEL, HB>(g, lc, x, b, y, c, q + 2, acc, pshare, ps);
+    zm_step<T, G, D, 0, VEL, HB>(g, lc, x, px, b, y, c, q, acc, pshare, ps);
+    if (q + 1 < nq) zm_step<T, G, D, 1, VEL, HB>(g, lc, x, px, b, y, c, q + 1, acc, pshare, ps);
+    if (q + 2 < nq) zm_step<T, G, D, 2, VEL, HB>(g, lc, x, px, b, y, c, q + 2, acc, pshare, ps);
   }
 }
 
 template <typename T, int G>
 __device__ __forceinline__ void prow_bnd_split(const Geom& g, const LevelConst<T>& lc, const T* __restrict__ x,
-                                               const T* __restrict__ b, T* __restrict__ y, int has_b,
+                                               const T* __restrict__ px, const T* __restrict__ b, T* __restrict__ y, int has_b,
                                                const int* __restrict__ bnd, int nbnd, int nmain, PStep<T> ps,
                                                T (*red)[kZmCols]);
 
 template <typename T, int G, bool VEL, bool HB>
 __global__ void __launch_bounds__(3 * kZmCols) k_apply_zm(Geom g, LevelConst<T> lc, const T* __restrict__ x,
-                                                          const T* __restrict__ b, T* __restrict__ y, int kc, int ncb,
+                                                          const T* __restrict__ px, const T* __restrict__ b,
+                                                          T* __restrict__ y, int kc, int ncb,
                                                           const int* __restrict__ bnd, int nbnd, int nmain,
                                                           PStep<T> ps) {
   __shared__ T pshare[2][3][kZmCols];
   if ((int)blockIdx.x >= nmain) {
-    prow_bnd_split<T, G>(g, lc, x, b, y, (int)HB, bnd, nbnd, nmain, ps, pshare[0]);
+    prow_bnd_split<T, G>(g, lc, x, px, b, y, (int)HB, bnd, nbnd, nmain, ps, pshare[0]);
     return;
   }
   const int lin = xcd_block_of(nmain);
@@ -464,19 +465,18 @@ __global__ void __launch_bounds__(3 * kZmCols) k_apply_zm(Geom g, LevelConst<T> 
   for (int dj = -1; dj <= 1; ++dj) c.nb[dj + 1] = min(max(c.col + dj * n1, 0), ncol - 1);
   const int wave = threadIdx.x / kZmCols;  // velocity component
   if (wave == 0)
-    zm_run<T, G, 0, VEL, HB>(g, lc, x, b, y, c, pshare, ps);
+    zm_run<T, G, 0, VEL, HB>(g, lc, x, px, b, y, c, pshare, ps);
   else if (wave == 1)
-    zm_run<T, G, 1, VEL, HB>(g, lc, x, b, y, c, pshare, ps);
+    zm_run<T, G, 1, VEL, HB>(g, lc, x, px, b, y, c, pshare, ps);
   else
-    zm_run<T, G, 2, VEL, HB>(g, lc, x, b, y, c, pshare, ps);
+    zm_run<T, G, 2, VEL, HB>(g, lc, x, px, b, y, c, pshare, ps);
 }
 
 // Pressure rows at boundary nodes (list), boundary-class stencils.
 template <typename T, int G>
 __device__ __forceinline__ void prow_bnd_block(const Geom& g, const LevelConst<T>& lc, const T* __restrict__ x,
                                                const T* __restrict__ b, T* __restrict__ y, int opmask, int has_b,
-                                               const int* __restrict__ bnd, int nbnd, int nmain, int bs,
-                                               PStep<T> ps) {
+                                               const int* __restrict__ bnd, int nbnd, int nmain, int bs) {
   const int q = ((int)blockIdx.x - nmain) * bs + (int)threadIdx.x;
   if (q >= nbnd) return;
   const int t = bnd[q];
@@ -484,14 +484,8 @@ __device__ __forceinline__ void prow_bnd_block(const Geom& g, const LevelConst<T
   decode(t, g.n1, i, j, k);
   const T acc = prow_value<T, G>(g, lc, x, opmask, t, i, j, k);
   const int pp = 3 * g.vstride + t;
-  const T r = has_b ? b[pp] - acc : acc;
-  if (ps.p)
-    ps.p[t] -= ps.omega * ps.dinv[t] * r;
-  else
-    y[pp] = r;
+  y[pp] = has_b ? b[pp] - acc : acc;
 }
-
-
 
 // The boundary pressure rows of a k-marching launch, one component per
 // wavefront: the block's three wavefronts take the same 64 nodes, wavefront d
@@ -500,7 +494,7 @@ __device__ __forceinline__ void prow_bnd_block(const Geom& g, const LevelConst<T
 // loads of a whole row per thread.  red: 3 x 64 words of LDS.
 template <typename T, int G>
 __device__ __forceinline__ void prow_bnd_split(const Geom& g, const LevelConst<T>& lc, const T* __restrict__ x,
-                                               const T* __restrict__ b, T* __restrict__ y, int has_b,
+                                               const T* __restrict__ px, const T* __restrict__ b, T* __restrict__ y, int has_b,
                                                const int* __restrict__ bnd, int nbnd, int nmain, PStep<T> ps,
                                                T (*red)[kZmCols]) {
   const int lane = (int)threadIdx.x % kZmCols, d = (int)threadIdx.x / kZmCols;
@@ -539,7 +533,7 @@ __device__ __forceinline__ void prow_bnd_split(const Geom& g, const LevelConst<T
   if (d != 0 || q >= nbnd) return;
   T ac = 0;
   if constexpr (G == 1) {
-    const T* __restrict__ p = x + 3 * (size_t)g.vstride;
+    const T* __restrict__ p = px;
     HHG_BCLS_CASES(p1, HHG_CROW)
   }
   // opmask of the k-marching launch: B and -C p (PSPG) / B only (Taylor-Hood)
@@ -547,7 +541,7 @@ __device__ __forceinline__ void prow_bnd_split(const Geom& g, const LevelConst<T
   const int pp = 3 * g.vstride + t;
   const T r = has_b ? b[pp] - acc : acc;
   if (ps.p)
-    ps.p[t] -= ps.omega * ps.dinv[t] * r;
+    ps.pout[t] = ps.p[t] - ps.omega * ps.dinv[t] * r;
   else
     y[pp] = r;
 }
@@ -570,7 +564,7 @@ __global__ void __launch_bounds__(3 * kZmCols) k_prow_split(Geom g, LevelConst<T
                                                             PStep<T> ps) {
   __shared__ T red[3][kZmCols];
   if ((int)blockIdx.x >= ninner) {
-    prow_bnd_split<T, 8>(g, lc, x, b, y, 1, bnd, nbnd, ninner, ps, red);
+    prow_bnd_split<T, 8>(g, lc, x, x + 3 * (size_t)g.vstride, b, y, 1, bnd, nbnd, ninner, ps, red);
     return;
   }
   const int lane = (int)threadIdx.x % kZmCols, d = (int)threadIdx.x / kZmCols;
@@ -597,7 +591,7 @@ __global__ void __launch_bounds__(3 * kZmCols) k_prow_split(Geom g, LevelConst<T
   const int pp = 3 * g.vstride + t;
   const T r = b[pp] - acc;
   if (ps.p)
-    ps.p[t] -= ps.omega * ps.dinv[t] * r;
+    ps.pout[t] = ps.p[t] - ps.omega * ps.dinv[t] * r;
   else
     y[pp] = r;
 }
@@ -1897,9 +1891,10 @@ static double p_sites(const Geom& g) {
 }
 
 template <typename T>
-void launch_apply(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const Tables<T>* tb, const T* x, const T* b,
-                  T* y, int opmask, bool has_b, bool vel_rows, bool p_rows, const int* bnd, int nbnd,
-                  const PStep<T>& ps) {
+static void apply_launch(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const T* x, const T* b, T* y,
+                         int opmask, bool has_b, bool vel_rows, bool p_rows, const int* bnd, int nbnd,
+                         const PStep<T>& ps) {
+  const T* px = ps.p ? ps.p : x + 3 * (size_t)g.vstride;
   if (!(vel_rows || p_rows)) return;
   KScope ks(s, KF_APPLY, p_sites(g));
   const int hb = has_b, vr = vel_rows, pr = p_rows;
@@ -1936,8 +1931,6 @@ void launch_apply(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const T
     // float64 at 114 VGPRs would hold 5 workgroups per CU; the same cap to 3
     // measured 2.158 -> 2.102 ms on the n1 = 257 lattice (4: 2.135 ms)
     const unsigned dyn = g.G == 8 && g.n1 >= 200 ? kZmF32Lds : 0;
-    // the fused pressure step: the pressure-residual form only
-    const bool fused = ps.p && !vel_rows && has_b;
     // Taylor-Hood pressure residual on lattices up to 33 nodes per edge: the
     // per-node split form (6-tet FMG to level 5: 3.206 -> 3.187 ms; the same
     // up to 65 nodes: 3.186 ms)
@@ -1952,8 +1945,8 @@ void launch_apply(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const T
     auto go = [&](auto gg, auto vel, auto hbc) {
       constexpr int GG = decltype(gg)::value;
       constexpr bool V = decltype(vel)::value, H = decltype(hbc)::value;
-      hipLaunchKernelGGL((k_apply_zm<T, GG, V, H>), grid, block, dyn, s, g, lc, x, b, y, kc, ncb, bnd, nb_bnd, nmain,
-                         fused ? ps : PStep<T>{});
+      hipLaunchKernelGGL((k_apply_zm<T, GG, V, H>), grid, block, dyn, s, g, lc, x, px, b, y, kc, ncb, bnd, nb_bnd,
+                         nmain, ps);
     };
     using I1 = std::integral_constant<int, 1>;
     using I8 = std::integral_constant<int, 8>;
@@ -1970,8 +1963,6 @@ void launch_apply(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const T
       else
         hb ? go(I8{}, BF{}, BT{}) : go(I8{}, BF{}, BF{});
     }
-    if (ps.p && !fused)
-      HHG_LAUNCH((k_pstep<T>), nblocks(g.nn), s, g.nn, ps.dinv, ps.p, y + 3 * (size_t)g.vstride, ps.omega);
   } else {
     const int nmain = (int)nblocks8(g.nn);
     const unsigned nb = (unsigned)(nmain + (nb_bnd + kBlock - 1) / kBlock);
@@ -1986,10 +1977,19 @@ void launch_apply(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const T
       else
         HHG_LAUNCH((k_apply<T, 8, false>), nb, s, g, lc, x, b, y, opmask, hb, vr, pr, bnd, nb_bnd, nmain);
     }
-    if (ps.p)  // the per-site form stores the residual; the step follows
-      HHG_LAUNCH((k_pstep<T>), nblocks(g.nn), s, g.nn, ps.dinv, ps.p, y + 3 * (size_t)g.vstride, ps.omega);
   }
-  (void)tb;
+}
+template <typename T>
+void launch_apply(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const Tables<T>*, const T* x, const T* b,
+                  T* y, int opmask, bool has_b, bool vel_rows, bool p_rows, const int* bnd, int nbnd) {
+  apply_launch<T>(s, g, lc, x, b, y, opmask, has_b, vel_rows, p_rows, bnd, nbnd, PStep<T>{});
+}
+template <typename T>
+void launch_uzawa_pressure(hipStream_t s, const Geom& g, const LevelConst<T>& lc, const T* x, const T* b, T* r,
+                           const int* bnd, int nbnd, const PStep<T>& ps) {
+  LevelConst<T> c = lc;
+  c.nu = c.ainv_site = nullptr;
+  apply_launch<T>(s, g, c, x, b, r, g.G == 1 ? 15 : 7, true, false, true, bnd, nbnd, ps);
 }
 
 // Launch, with the packet-stamped events of a KScope opened with packet = true.
@@ -2366,7 +2366,9 @@ void launch_axpy(hipStream_t s, T* y, const T* x, size_t n, T a) {
 
 #define HHG_INSTANTIATE(T)                                                                                          \
   template void launch_apply<T>(hipStream_t, const Geom&, const LevelConst<T>&, const Tables<T>*, const T*,        \
-                                const T*, T*, int, bool, bool, bool, const int*, int, const PStep<T>&);             \
+                                const T*, T*, int, bool, bool, bool, const int*, int);                              \
+  template void launch_uzawa_pressure<T>(hipStream_t, const Geom&, const LevelConst<T>&, const T*, const T*, T*,    \
+                                         const int*, int, const PStep<T>&);                                         \
   template void launch_gs_colour<T>(hipStream_t, const Geom&, const LevelConst<T>&, T*, const T*, int);             \
   template void launch_pressure_step<T>(hipStream_t, const Geom&, const T*, T*, const T*, T);                       \
   template void launch_schur_diag<T>(hipStream_t, const Geom&, const Tables<T>*, const T*, int, T*,                 \

@@ -33,10 +33,25 @@ def _oracle(vorder, N, varnu):
     return _ORACLE[vorder, N, varnu]
 
 
-@pytest.mark.parametrize("gs,xi,iters", [(hhg.HHG_GS_FWD, 3, 1), (hhg.HHG_GS_FWD, 1, 2), (hhg.HHG_GS_SYM, 1, 1)])
+FWD, SYM = hhg.HHG_GS_FWD, hhg.HHG_GS_SYM
+
+
+@pytest.mark.parametrize("gs,xi,iters", [(FWD, 3, 1), (FWD, 1, 2), (SYM, 1, 1)])
 @pytest.mark.parametrize("disc,L", [(P1, 3), (P1, 4), (P2, 2), (P2, 3), (P2, 4), (P2, 5)])
 @pytest.mark.parametrize("varnu", [False, True])
 def test_smooth_boxes(disc, L, gs, xi, iters, varnu):
+    _check(disc, L, gs, xi, iters, varnu)
+
+
+# the P1 lattices whose sweeps are cut into runs: every length of run and both
+# first colours (the pressure alternates between two buffers as well)
+@pytest.mark.parametrize("gs,xi,iters", [(FWD, 3, 1), (FWD, 2, 1), (FWD, 1, 2), (SYM, 1, 1), (SYM, 2, 2)])
+@pytest.mark.parametrize("L,varnu", [(5, False), (5, True), (6, False)])
+def test_smooth_runs_p1(L, gs, xi, iters, varnu):
+    _check(P1, L, gs, xi, iters, varnu)
+
+
+def _check(disc, L, gs, xi, iters, varnu):
     vorder = 1 if disc == P1 else 2
     U = _oracle(vorder, 2 ** L, varnu)
     n = U.S.n
