@@ -17,6 +17,15 @@ struct BoxRows<1> {
   static __device__ __forceinline__ T BT(P p, int d) {
     return gen::p1_BTs<T, GR, S1, S2>(p, d);
   }
+  // the same over three planes of a ring
+  template <typename T, int GR, int S1, int SG, typename P>
+  static __device__ __forceinline__ T Ar(const P (&u)[3]) {
+    return gen::p1_Ar<T, GR, S1, SG>(u);
+  }
+  template <typename T, int GR, int S1, typename P>
+  static __device__ __forceinline__ T BTr(const P (&p)[3], int d) {
+    return gen::p1_BTr<T, GR, S1>(p, d);
+  }
   // element-wise row of the variable-viscosity A (units of h): u the site's
   // word, nu the viscosity of the site's P1 index
   template <typename T, int GR, int S1, int S2, int SG>
@@ -36,6 +45,14 @@ struct BoxRows<8> {
   template <typename T, int GR, int S1, int S2, typename P>
   static __device__ __forceinline__ T BT(P p, int d) {
     return gen::p2_BTs<T, GR, S1, S2>(p, d);
+  }
+  template <typename T, int GR, int S1, int SG, typename P>
+  static __device__ __forceinline__ T Ar(const P (&u)[3]) {
+    return gen::p2_Ar<T, GR, S1, SG>(u);
+  }
+  template <typename T, int GR, int S1, typename P>
+  static __device__ __forceinline__ T BTr(const P (&p)[3], int d) {
+    return gen::p2_BTr<T, GR, S1>(p, d);
   }
   template <typename T, int GR, int S1, int S2, int SG>
   static __device__ __forceinline__ T Anu(const T* u, const T* nu) {

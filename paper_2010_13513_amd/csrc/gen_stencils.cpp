@@ -570,6 +570,43 @@ void emit_box_rows(FILE* f, const ElementSet& es, const char* D, int G) {
       std::fprintf(f, "  return a + b;\n}\n");
     }
   }
+  // the same over the planes k - 1, k, k + 1 of a ring: u[dk + 1] (p[dk + 1])
+  // the site's position in plane k + dk
+  for (int g = 0; g < G; ++g) {
+    std::fprintf(f,
+                 "template <typename T, int S1, int SG, typename P>\n__device__ __forceinline__ T %s_Ar_g%d(const P (&u)[3]) {\n"
+                 "  T a = 0, b = 0;\n",
+                 D, g);
+    int q = 0;
+    for (auto& e : pruned(es, 'A', g, 1))
+      std::fprintf(f, "  %s = fma(T(%s), u[%d][(%d) * SG + (%d) + (%d) * S1], %s);\n", q & 1 ? "b" : "a",
+                   lit(std::nearbyint(e.w[0] * da)).c_str(), e.dk + 1, e.g - g, e.di, e.dj, q & 1 ? "b" : "a"),
+          ++q;
+    std::fprintf(f, "  return a + b;\n}\n");
+    for (int d = 0; d < 3; ++d) {
+      std::fprintf(f,
+                   "template <typename T, int S1, typename P>\n__device__ __forceinline__ T %s_BTr_g%d_d%d(const P (&p)[3]) {\n"
+                   "  T a = 0, b = 0;\n",
+                   D, g, d);
+      q = 0;
+      for (auto& e : pruned(es, 'T', g, 3)) {
+        if (std::fabs(e.w[d]) < 1e-13) continue;
+        std::fprintf(f, "  %s = fma(T(%s), p[%d][(%d) + (%d) * S1], %s);\n", q & 1 ? "b" : "a",
+                     lit(std::nearbyint(e.w[d] * dt)).c_str(), e.dk + 1, e.di, e.dj, q & 1 ? "b" : "a");
+        ++q;
+      }
+      std::fprintf(f, "  return a + b;\n}\n");
+    }
+  }
+  std::fprintf(f, "template <typename T, int GR, int S1, int SG, typename P>\n__device__ __forceinline__ T %s_Ar(const P (&u)[3]) {\n", D);
+  for (int g = 0; g < G; ++g) std::fprintf(f, "  if constexpr (GR == %d) return %s_Ar_g%d<T, S1, SG>(u);\n", g, D, g);
+  std::fprintf(f, "}\ntemplate <typename T, int GR, int S1, typename P>\n__device__ __forceinline__ T %s_BTr(const P (&p)[3], int d) {\n", D);
+  for (int g = 0; g < G; ++g)
+    std::fprintf(f,
+                 "  if constexpr (GR == %d) return d == 0 ? %s_BTr_g%d_d0<T, S1>(p) : (d == 1 ? %s_BTr_g%d_d1<T, S1>(p) "
+                 ": %s_BTr_g%d_d2<T, S1>(p));\n",
+                 g, D, g, D, g, D, g);
+  std::fprintf(f, "}\n");
   std::fprintf(f, "template <typename T, int GR, int S1, int S2, int SG, typename P>\n__device__ __forceinline__ T %s_As(P u) {\n", D);
   for (int g = 0; g < G; ++g) std::fprintf(f, "  if constexpr (GR == %d) return %s_As_g%d<T, S1, S2, SG>(u);\n", g, D, g);
   std::fprintf(f, "}\ntemplate <typename T, int GR, int S1, int S2, typename P>\n__device__ __forceinline__ T %s_BTs(P p, int d) {\n", D);
@@ -635,6 +672,19 @@ void emit_sequence(FILE* f, const ElementSet& es, int G, const std::string& name
     if (need[g].any) all.add(need[g].lo, need[g].hi);
   all.add(pb.lo, pb.hi);
   all.add(nb.lo, nb.hi);
+  // marching along k with the steps in flight together: at iteration q step s
+  // updates plane q - skew[s].  A step must find the earlier steps' values at
+  // every plane its row reads (done in an earlier iteration), and must not
+  // have passed a plane that an earlier step still reads as old.
+  std::vector<int> skew(seq.size(), 0);
+  for (size_t q = 0; q < seq.size(); ++q)
+    for (size_t e = 0; e < q; ++e) {
+      const int g = group(seq[q]), ge = group(seq[e]);
+      for (auto& en : pruned(es, 'A', g, 1))
+        if (en.g == ge) skew[q] = std::max(skew[q], skew[e] + 1 + en.dk);
+      for (auto& en : pruned(es, 'A', ge, 1))
+        if (en.g == g) skew[q] = std::max(skew[q], skew[e] + 1 - en.dk);
+    }
   auto arr = [&](const int* v) {
     return "{" + std::to_string(v[0]) + ", " + std::to_string(v[1]) + ", " + std::to_string(v[2]) + "}";
   };
@@ -650,6 +700,9 @@ void emit_sequence(FILE* f, const ElementSet& es, int G, const std::string& name
   for (int g = 0; g < G; ++g) std::fprintf(f, "%d, ", wr[g]);
   std::fprintf(f, "};\n  static constexpr int used[%d] = {", G);
   for (int g = 0; g < G; ++g) std::fprintf(f, "%d, ", need[g].any ? 1 : 0);
+  std::fprintf(f, "};\n");
+  std::fprintf(f, "  static constexpr int skew[%zu] = {", skew.size());
+  for (int z : skew) std::fprintf(f, "%d, ", z);
   std::fprintf(f, "};\n");
   table("lo", step, false);
   table("hi", step, true);

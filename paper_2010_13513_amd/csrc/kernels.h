@@ -204,7 +204,8 @@ void launch_gs_colour(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* 
 // iteration with the velocity groups alternating between x and alt (bit g of
 // in_alt: group g is in alt; all bits equal between calls).  Level: the same
 // in place, one launch.  p: the pressures.
-bool gs_runs_supported(const Geom& g, int xi, bool sym);
+template <typename T>
+bool gs_runs_supported(const Geom& g, bool varnu, int xi, bool sym);
 bool gs_level_supported(const Geom& g, int xi, bool sym);
 template <typename T>
 void launch_gs_runs(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* p, const T* b,

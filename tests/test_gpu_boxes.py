@@ -51,6 +51,39 @@ def test_smooth_runs_p1(L, gs, xi, iters, varnu):
     _check(P1, L, gs, xi, iters, varnu)
 
 
+# the lattices whose runs march along k (constant coefficients), against the
+# variable-viscosity kernels with a viscosity of one (a launch per colour for
+# Taylor-Hood, boxes for P1: checked against the oracle on smaller lattices);
+# every word, boundary values and padding included
+@pytest.mark.parametrize("gs,xi,iters", [(FWD, 3, 1), (FWD, 1, 2), (SYM, 1, 1)])
+@pytest.mark.parametrize("disc,L,prec", [(P2, 6, hhg.HHG_F64), (P2, 7, hhg.HHG_F64), (P2, 7, hhg.HHG_F32),
+                                         (P1, 7, hhg.HHG_F64), (P1, 7, hhg.HHG_F32), (P1, 8, hhg.HHG_F64),
+                                         (P1, 8, hhg.HHG_F32)])
+def test_smooth_runs_along_k(disc, L, prec, gs, xi, iters):
+    out = []
+    for varnu in (False, True):
+        lib = Lib(disc, L - 1, L)
+        torch = lib.torch
+        try:
+            if varnu:
+                hhg.hhg_set_viscosity(lib.h, L, torch.ones((2 ** L + 1) ** 3, dtype=torch.float64, device=lib.dev))
+            dt = torch.float64 if prec == hhg.HHG_F64 else torch.float32
+            gen = torch.Generator(device=lib.dev).manual_seed(13513 + 10 * L + xi)
+            x = torch.randn(lib.empty(L, dt).shape, generator=gen, dtype=dt, device=lib.dev)
+            b = torch.randn(x.shape, generator=gen, dtype=dt, device=lib.dev)
+            hhg.hhg_smooth(lib.h, L, x, b, iters, gs, xi, 2.3, prec)
+            torch.cuda.synchronize()
+            out.append(x)
+            nv, np_ = lib.layout(L)[:2]
+        finally:
+            lib.close()
+    got, want = out
+    tol = 1e-12 if prec == hhg.HHG_F64 else 500 * 2.0 ** -24
+    split = got.numel() - np_
+    for part in (slice(0, split), slice(split, None)):
+        assert float((got[part] - want[part]).abs().max()) <= tol * float(want[part].abs().max())
+
+
 def _check(disc, L, gs, xi, iters, varnu):
     vorder = 1 if disc == P1 else 2
     U = _oracle(vorder, 2 ** L, varnu)
