@@ -2222,19 +2222,6 @@ size_t check_train_args(hhg_mlp m, const float* x, const float* y, int n_samples
     HHG_REQUIRE(order[q] >= 0 && order[q] < n_samples, HHG_ERR_ARG, "sample index out of range");
   return nord;
 }
-// The Adam steps of every full minibatch of every epoch, enqueued on the
-// context stream: dord = the order on the device, dloss[e] += batch losses of
-// epoch e (zeroed by the caller).
-void train_steps(hhg_mlp m, const float* x, const float* y, int n_samples, int batch, int epochs, float lr,
-                 const int* dord, double* dloss) {
-  hipStream_t s = m->ctx->stream;
-  const int nb = n_samples / batch;
-  for (int e = 0; e < epochs; ++e)
-    for (int q = 0; q < nb; ++q) {
-      const int* idx = dord + (size_t)e * n_samples + (size_t)q * batch;
-      m->net.train_step_dev(s, x, y, idx, batch, lr, dloss + e);
-    }
-}
 }  // namespace
 }  // namespace hhg
 
@@ -2257,7 +2244,7 @@ hhg_status hhg_mlp_train(hhg_mlp m, const float* x, const float* y, int n_sample
     std::vector<double> hloss(epochs, 0.0);
     hipError_t err = hipMemcpyAsync(dord, order, nord * sizeof(int), hipMemcpyHostToDevice, s);
     if (err == hipSuccess) err = hipMemcpyAsync(dloss, hloss.data(), epochs * sizeof(double), hipMemcpyHostToDevice, s);
-    if (err == hipSuccess) train_steps(m, x, y, n_samples, batch, epochs, lr, dord, dloss);
+    if (err == hipSuccess) m->net.train_dev(s, x, y, n_samples, batch, epochs, lr, dord, dloss);
     if (err == hipSuccess) err = hipMemcpyAsync(hloss.data(), dloss, epochs * sizeof(double), hipMemcpyDeviceToHost, s);
     if (err == hipSuccess) err = hipStreamSynchronize(s);
     (void)hipFree(dord);
@@ -2281,7 +2268,7 @@ hhg_status hhg_mlp_train_noalloc(hhg_mlp m, const float* x, const float* y, int 
     int* dord = (int*)(m->ctx->scratch + kScratchEpochs * sizeof(double));
     launch_fill<double>(s, dloss, (size_t)epochs, 0.0);  // the previous call left its losses here
     HHG_CHECK_HIP(hipMemcpyAsync(dord, order, nord * sizeof(int), hipMemcpyHostToDevice, s));
-    train_steps(m, x, y, n_samples, batch, epochs, lr, dord, dloss);
+    m->net.train_dev(s, x, y, n_samples, batch, epochs, lr, dord, dloss);
     double last = 0.0;
     HHG_CHECK_HIP(hipMemcpyAsync(&last, dloss + (epochs - 1), sizeof(double), hipMemcpyDeviceToHost, s));
     HHG_CHECK_HIP(hipStreamSynchronize(s));

@@ -230,3 +230,45 @@ def test_fallback_fires_on_bad_network_and_solve_converges():
             hhg.hhg_mlp_destroy(m)
     finally:
         lib.close()
+
+
+@pytest.mark.parametrize("n_in,H,n_out,B,steps", [(37, 32, 21, 20, 3), (70, 48, 16, 1, 2), (331, 64, 206, 48, 3),
+                                                 (130, 128, 33, 72, 4)])
+def test_training_steps_match_adam(ctx, n_in, H, n_out, B, steps):
+    """A training step against Adam in float64 on the gradients of
+    hhg_mlp_loss_grad (tested above) at the same parameters, and a call of
+    several steps (minibatches alternate between two input buffers) against
+    calls of one step, bit for bit.  An update is at most a few lr = 1e-3 and
+    carries some ten float32 roundings of its own terms, the new parameter one
+    more: 1e-8 + 2^-23 max(|p|, 1)."""
+    torch, c = ctx
+    rng = np.random.default_rng(B)
+    p0 = _flat(omlp.init_params(rng, n_in, H, n_out))
+    n = B * steps
+    X = torch.from_numpy(rng.standard_normal((n, n_in)).astype(np.float32)).cuda()
+    Y = torch.from_numpy(rng.standard_normal((n, n_out)).astype(np.float32)).cuda()
+    order = rng.permutation(n).astype(np.int32)
+    one, many = (hhg.hhg_mlp_create(c, n_in, H, n_out, B) for _ in range(2))
+    try:
+        for m in (one, many):
+            hhg.hhg_mlp_set_params(m, p0)
+        p, mo, vo = p0.astype(np.float64), 0.0, 0.0
+        losses = []
+        for k in range(steps):
+            rows = torch.from_numpy(order[k * B:(k + 1) * B].astype(np.int64)).cuda()
+            x, y = X[rows].contiguous(), Y[rows].contiguous()
+            want_loss, g = hhg.hhg_mlp_loss_grad(one, x, y, B)
+            g = g.astype(np.float64)
+            mo, vo = 0.9 * mo + 0.1 * g, 0.999 * vo + 0.001 * g * g
+            want = p - 1e-3 * (mo / (1 - 0.9 ** (k + 1))) / (np.sqrt(vo / (1 - 0.999 ** (k + 1))) + 1e-8)
+            loss = hhg.hhg_mlp_train(one, x, y, B, B, 1, 1e-3, np.arange(B, dtype=np.int32))
+            assert abs(loss - want_loss) <= 1e-12 * want_loss
+            losses.append(loss)
+            p = hhg.hhg_mlp_get_params(one).astype(np.float64)
+            assert (np.abs(p - want) <= 1e-8 + 2.0 ** -23 * np.maximum(np.abs(want), 1.0)).all(), k
+        loss = hhg.hhg_mlp_train(many, X, Y, n, B, 1, 1e-3, order)
+        assert abs(loss - np.mean(losses)) <= 1e-12 * loss
+        assert np.array_equal(hhg.hhg_mlp_get_params(many), hhg.hhg_mlp_get_params(one))
+    finally:
+        for m in (one, many):
+            hhg.hhg_mlp_destroy(m)
