@@ -733,11 +733,25 @@ void u_smooth(hhg_hier h, int l, double* x, const double* b, int iters, int gs, 
   if ((long)U.L.ncell * U.L.P <= h->ufused_slots &&
       launch_u_smooth_nodes(S(h), U, x, b, iters, xi, gs == HHG_GS_SYM, omega))
     return;
+  // A symmetric sweep turns at its first and last colour; a colour next to
+  // itself is idempotent (its rows do not couple) and taken once.
+  const bool sym = gs == HHG_GS_SYM;
+  const int K = U.ncol_if, per = sym ? 2 * ncol - 2 : ncol, total = xi > 0 ? xi * per + (sym ? 1 : 0) : 0;
+  auto colour_at = [&](int q) {
+    const int r = q % per;
+    return r < ncol ? r : per - r;
+  };
   for (int it = 0; it < iters; ++it) {
-    for (int s = 0; s < xi; ++s) {
-      for (int c = 0; c < ncol; ++c) u_colour(h, l, c, x, b);
-      if (gs == HHG_GS_SYM)
-        for (int c = ncol - 1; c >= 0; --c) u_colour(h, l, c, x, b);
+    for (int q = 0; q < total;) {
+      if (!U.ipts || colour_at(q) < K) {
+        u_colour(h, l, colour_at(q++), x, b);
+        continue;
+      }
+      unsigned seq = 0;
+      int steps = 0;
+      for (; q < total && steps < 16 && colour_at(q) >= K; ++q, ++steps)
+        seq |= (unsigned)(colour_at(q) - K) << 2 * steps;
+      launch_u_gs_cells(S(h), U, seq, steps, x, b);
     }
     // r_p = g - B u + C p, then p -= omega D^{-1} r_p
     launch_u_apply_rows(S(h), U.L, U.inner, U.zitems, U.lst, x, b, r, 12, true, false, false, true);

@@ -27,11 +27,36 @@ __device__ __forceinline__ void unpack(int v, int& i, int& j, int& k) {
   k = v >> 20;
 }
 
-// Slot offsets of the 15 stencil points relative to the centre.
-__device__ __forceinline__ void offsets(int i, int j, int k, int n, int (&off)[kUPoints]) {
-  const int c = uslot(i, j, k, n);
+// Slot offsets of the 15 stencil points of an interior point relative to the
+// centre: a step in j (up n - j, down n + 1 - j) and in k (the plane's rows)
+// add up, as the directions' signs agree.
+__device__ __forceinline__ void offsets(int j, int k, int n, int (&off)[kUPoints]) {
+  const int jp = n - j, jm = jp + 1;
+  const int kp = (n + 1 - k) * (n + 2 - k) / 2 - (n + 1) + k, km = kp + n + 1 - k;
 #pragma unroll
-  for (int e = 0; e < kUPoints; ++e) off[e] = uslot(i + udir(e, 0), j + udir(e, 1), k + udir(e, 2), n) - c;
+  for (int e = 0; e < kUPoints; ++e) {
+    const int dj = udir(e, 1), dk = udir(e, 2);
+    off[e] = udir(e, 0) + dj * (dj > 0 ? jp : jm) + dk * (dk > 0 ? kp : km);
+  }
+}
+
+// The 15 words: neighbours in i are neighbours in memory, taken two to a load.
+typedef double v2d __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ void words(const double* __restrict__ x, const int (&off)[kUPoints],
+                                      double (&v)[kUPoints]) {
+  auto two = [&](int e0, int e1) {
+    const v2d t = *reinterpret_cast<const v2d*>(x + off[e0]);
+    v[e0] = t.x;
+    v[e1] = t.y;
+  };
+  two(8, 0);
+  v[1] = x[off[1]];
+  two(2, 3);
+  two(4, 5);
+  two(6, 7);
+  two(10, 9);
+  two(12, 11);
+  two(14, 13);
 }
 
 // Interior rows of cell c (class 0) into LDS: A, B^T (3), B (3), M.
@@ -59,7 +84,7 @@ __device__ __forceinline__ void apply_inner_pt(const ULev& L, int c, const doubl
                                                int wv, int wp) {
   const int n = L.n;
   int off[kUPoints];
-  offsets(i, j, k, n, off);
+  offsets(j, k, n, off);
   const size_t t = (size_t)c * L.P + uslot(i, j, k, n);
   const size_t vs = L.vs;
   if (MASS) {
@@ -368,21 +393,25 @@ __global__ void __launch_bounds__(kUBlock) k_u_apply_iface(ULev L, UList lst, co
 // ----------------------------------------------------------- Gauss-Seidel
 // One interior colour: points (i, j, k) of the cell interiors with i + j + k
 // = colour (mod 4), segments of stride 4; u_d += (f_d - A u_d - B^T_d p) / a_00.
+// Bound by the loads' addresses (a lane is 32 bytes from the next): 24 cells of
+// 64 intervals 42 -> 31 us per colour with 32 loads of one or two words per
+// point instead of 60 and the slots of a point from four strides; a component
+// per thread (48 loads, twice the wavefronts in flight) 36 us.
 __device__ __forceinline__ void gs_inner_pt(const ULev& L, int c, const double (*w)[kUPoints], double ai, int i,
                                             int j, int k, double* __restrict__ x, const double* __restrict__ b) {
   const int n = L.n;
   int off[kUPoints];
-  offsets(i, j, k, n, off);
+  offsets(j, k, n, off);
   const size_t t = (size_t)c * L.P + uslot(i, j, k, n);
   const size_t vs = L.vs;
-  const double* p = x + 3 * vs + t;
-  double r[3] = {b[t], b[vs + t], b[2 * vs + t]};
+  double r[3] = {b[t], b[vs + t], b[2 * vs + t]}, v[4][kUPoints];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) words(x + f * vs + t, off, v[f]);
 #pragma unroll
   for (int e = 0; e < kUPoints; ++e) {
-    const double pe = p[off[e]];
-    r[0] -= w[0][e] * x[t + off[e]] + w[1][e] * pe;
-    r[1] -= w[0][e] * x[vs + t + off[e]] + w[2][e] * pe;
-    r[2] -= w[0][e] * x[2 * vs + t + off[e]] + w[3][e] * pe;
+    r[0] -= w[0][e] * v[0][e] + w[1][e] * v[3][e];
+    r[1] -= w[0][e] * v[1][e] + w[2][e] * v[3][e];
+    r[2] -= w[0][e] * v[2][e] + w[3][e] * v[3][e];
   }
 #pragma unroll
   for (int d = 0; d < 3; ++d) x[d * vs + t] += r[d] * ai;
@@ -399,6 +428,120 @@ __global__ void __launch_bounds__(kUBlock) k_u_gs_inner(ULev L, USegs sg, double
   const int4 s = sg.s[sid];
   if (lane >= s.w) return;
   gs_inner_pt(L, c, w, cs->ainv0, s.x + 4 * lane, s.y, s.z, x, b);
+}
+
+// A run of interior colours of one component of one cell, the cell's words in
+// LDS: given the interface, the cells' interiors do not couple, nor the
+// components given p.  f - B^T p of the thread's points stays in registers.
+// A launch per colour is bound by its latency and by the stride-4 accesses to
+// four arrays (24 cells of 32 intervals: 10.6 us per colour, 85 us per
+// symmetric sweep); here a colour is 15 LDS reads per point and a barrier
+// (24 us per symmetric sweep, which leaves out the colour that the turn would
+// repeat).  Cells of 64 intervals exceed the LDS.
+constexpr int kUCell = 640;
+constexpr int kUCellRounds = 2;  // points of a colour per thread
+__global__ void __launch_bounds__(kUCell) k_u_gs_cells(ULev L, const int* __restrict__ pts, int4 off0, int off4,
+                                                       unsigned seq, int steps, double* __restrict__ x,
+                                                       const double* __restrict__ b) {
+  extern __shared__ double lds[];
+  constexpr int R = kUCellRounds;
+  const int n = L.n, np = utet(n + 1), tid = threadIdx.x, nt = blockDim.x;
+  const int c = blockIdx.x / 3, d = blockIdx.x % 3;
+  double* const u = lds;
+  double* const p = lds + np;
+  double* const xu = x + d * L.vs + (size_t)c * L.P;
+  const double* const xp = x + 3 * L.vs + (size_t)c * L.P;
+  const double* const f = b + d * L.vs + (size_t)c * L.P;
+  const UCell* __restrict__ cs = L.cs + c;
+  // the cell's words in one batch of loads
+  constexpr int LD = (6545 + kUCell - 1) / kUCell;  // 32 intervals; at most 16: 969 words, 128 threads
+  static_assert(LD * 128 >= 969, "words per thread");
+  double lu[LD], lp[LD];
+#pragma unroll
+  for (int q = 0; q < LD; ++q) {
+    const int t = min(tid + q * nt, np - 1);
+    lu[q] = xu[t];
+    lp[q] = xp[t];
+  }
+  int pt[4][R];
+  double g[4][R];
+  const int off[5] = {off0.x, off0.y, off0.z, off0.w, off4};
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int at = off[r] + tid + q * nt;
+      pt[r][q] = at < off[r + 1] ? pts[at] : -1;
+      g[r][q] = 0.0;
+      if (pt[r][q] >= 0) {
+        int i, j, k;
+        unpack(pt[r][q], i, j, k);
+        g[r][q] = f[uslot(i, j, k, n)];
+      }
+    }
+#pragma unroll
+  for (int q = 0; q < LD; ++q)
+    if (tid + q * nt < np) {
+      u[tid + q * nt] = lu[q];
+      p[tid + q * nt] = lp[q];
+    }
+  double w[kUPoints];
+#pragma unroll
+  for (int e = 0; e < kUPoints; ++e) w[e] = cs->BT[0][e][d];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if (pt[r][q] >= 0) {
+        int i, j, k, o[kUPoints];
+        unpack(pt[r][q], i, j, k);
+        offsets(j, k, n, o);
+        const double* pq = p + uslot(i, j, k, n);
+        double v = 0.0;
+#pragma unroll
+        for (int e = 0; e < kUPoints; ++e) v = fma(w[e], pq[o[e]], v);
+        g[r][q] -= v;
+      }
+#pragma unroll
+  for (int e = 0; e < kUPoints; ++e) w[e] = cs->A[0][e];
+  const double ai = cs->ainv0;
+#pragma unroll 1
+  for (int st = 0; st < steps; ++st, seq >>= 2) {
+    auto colour = [&](const int (&ptr)[R], const double (&gr)[R]) {
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        if (ptr[q] >= 0) {
+          int i, j, k, o[kUPoints];
+          unpack(ptr[q], i, j, k);
+          offsets(j, k, n, o);
+          double* uq = u + uslot(i, j, k, n);
+          double v = gr[q], v1 = 0.0;
+#pragma unroll
+          for (int e = 0; e < kUPoints; e += 2) v = fma(-w[e], uq[o[e]], v);
+#pragma unroll
+          for (int e = 1; e < kUPoints; e += 2) v1 = fma(-w[e], uq[o[e]], v1);
+          uq[0] = fma(v + v1, ai, uq[0]);
+        }
+    };
+    switch (seq & 3u) {
+      case 0: colour(pt[0], g[0]); break;
+      case 1: colour(pt[1], g[1]); break;
+      case 2: colour(pt[2], g[2]); break;
+      default: colour(pt[3], g[3]); break;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if (pt[r][q] >= 0) {
+        int i, j, k;
+        unpack(pt[r][q], i, j, k);
+        const int t = uslot(i, j, k, n);
+        xu[t] = u[t];
+      }
 }
 
 // Free interface nodes [first, first + count) of one colour, a group of
@@ -472,7 +615,7 @@ __global__ void __launch_bounds__(kUBlock) k_u_restrict_inner(ULev Lf, ULev Lc, 
   if (lane >= s.w) return;
   const int i = s.x + lane, j = s.y, k = s.z;
   int off[kUPoints];
-  offsets(2 * i, 2 * j, 2 * k, Lf.n, off);
+  offsets(2 * j, 2 * k, Lf.n, off);
   const size_t tf = (size_t)c * Lf.P + uslot(2 * i, 2 * j, 2 * k, Lf.n);
   const size_t tc = (size_t)c * Lc.P + uslot(i, j, k, Lc.n);
 #pragma unroll
@@ -777,7 +920,7 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
   double* const la = lds + 9 * n;
   unsigned* const lc = reinterpret_cast<unsigned*>(la + (size_t)N.len * n);
   int* const sched = reinterpret_cast<int*>(lc + (size_t)(N.len / 2) * n);  // one period: first | count << 12 | len << 24
-  const int per = sym ? 2 * N.ncol : N.ncol;
+  const int per = sym ? 2 * N.ncol - 2 : N.ncol, total = xi * per + (sym ? 1 : 0);
   for (int t = tid; t < 4 * n; t += kUSmall) {
     const int f = t / n, q = t - f * n;
     u[t] = x[f * vs + N.own[q]];
@@ -786,7 +929,7 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
   for (int t = tid; t < N.len * n; t += kUSmall) la[t] = N.A[t];
   for (int t = tid; t < N.len / 2 * n; t += kUSmall) lc[t] = N.col[t];
   if (tid < per) {
-    const int c = tid < N.ncol ? tid : per - 1 - tid;
+    const int c = tid < N.ncol ? tid : per - tid;
     sched[tid] = N.off[c] | (N.off[c + 1] - N.off[c]) << 12 | N.clen[c] << 24;
   }
   __syncthreads();
@@ -800,7 +943,6 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
     if (wave < 3) {
       double* const ud = u + wave * n;
       const double* const gd = g + wave * n;
-      const int steps = xi * per;
       double w[16];
       unsigned k[8];
       auto fetch = [&](int s) {
@@ -812,7 +954,7 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
       int s0 = sched[0], s1 = sched[1 % per], r = 1 % per;
       fetch(s0);
 #pragma unroll 1
-      for (int st = 0; st < steps; ++st) {
+      for (int st = 0; st < total; ++st) {
         r = r + 1 < per ? r + 1 : 0;
         const int s2 = sched[r];
         const int q0 = s0 & 4095, m = (s0 >> 12) & 4095, len = s0 >> 24;
@@ -894,14 +1036,14 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
       gq = g[q];
     }
   };
-  const int per = sym ? 2 * N.ncol : N.ncol, steps = xi * per;
+  const int per = sym ? 2 * N.ncol - 2 : N.ncol, steps = xi * per + (sym ? 1 : 0);
   fetch(0);
   int r = 0;
 #pragma unroll 1
   for (int st = 0; st < steps; ++st) {
-    const int c = r < N.ncol ? r : per - 1 - r;
+    const int c = r < N.ncol ? r : per - r;
     r = r + 1 < per ? r + 1 : 0;
-    const int cn = r < N.ncol ? r : per - 1 - r;
+    const int cn = r < N.ncol ? r : per - r;
     const int q0 = N.off[c], m = N.off[c + 1] - q0, len = N.clen[c];
     double a = 0.0, a1 = 0.0;
     if (tid < m) {
@@ -1056,6 +1198,19 @@ void launch_u_gs_inner(hipStream_t s, const ULev& L, USegs seg, double* x, const
   hipLaunchKernelGGL(k_u_gs_inner, seg_grid(seg, L.ncell), dim3(kUBlock), 0, s, L, seg, x, b);
 }
 
+void launch_u_gs_cells(hipStream_t s, const ULevelData& U, unsigned seq, int steps, double* x, const double* b) {
+  if (U.ioff[4] == 0) return;
+  double pts = 0.0;
+  for (int q = 0; q < steps; ++q) {
+    const int c = (seq >> 2 * q) & 3;
+    pts += U.ioff[c + 1] - U.ioff[c];
+  }
+  KScope ks(s, KF_GS_VERTEX, pts * U.L.ncell);
+  const size_t lds = 2 * sizeof(double) * (size_t)utet(U.L.n + 1);
+  hipLaunchKernelGGL(k_u_gs_cells, dim3(3 * U.L.ncell), dim3(U.L.n > 16 ? kUCell : 128), lds, s, U.L, U.ipts,
+                     make_int4(U.ioff[0], U.ioff[1], U.ioff[2], U.ioff[3]), U.ioff[4], seq, steps, x, b);
+}
+
 void launch_u_gs_iface(hipStream_t s, const ULev& L, const UList& lst, int first, int count, int maxocc, double* x,
                        const double* b) {
   if (count <= 0) return;
@@ -1096,6 +1251,7 @@ bool launch_u_smooth_nodes(hipStream_t s, const ULevelData& U, double* x, const 
 }
 void u_kernel_attributes() {
   (void)hipFuncSetAttribute((const void*)k_u_smooth_nodes, hipFuncAttributeMaxDynamicSharedMemorySize, kUNodeLds);
+  (void)hipFuncSetAttribute((const void*)k_u_gs_cells, hipFuncAttributeMaxDynamicSharedMemorySize, kUNodeLds);
   (void)hipFuncSetAttribute((const void*)k_u_nodes_sweep, hipFuncAttributeMaxDynamicSharedMemorySize, kUNodeLds);
 }
 

@@ -121,6 +121,8 @@ struct ULevelData {
   UNodes nodes;                  // small levels
   UList lst{};
   USegs all{}, inner{}, colour[4]{};
+  const int* ipts = nullptr;     // interior points i | j << 10 | k << 20 of a cell, by colour (levels of k_u_gs_cells)
+  int ioff[5] = {0, 0, 0, 0, 0};  // colour c: points ioff[c] .. ioff[c + 1]
   USegs zitems{};                // k-marching items (j, i0, ka, kb) of the interior apply
   double* dinv = nullptr;        // per slot: 1 / Schur diagonal of its node
   double* ml_own = nullptr;      // per slot: lumped mass of its node at the owner slot, else 0
@@ -147,6 +149,10 @@ int if_slots(int maxocc, int n);
 void launch_u_apply_rows(hipStream_t s, const ULev& L, USegs inner, USegs zitems, const UList& lst, const double* x,
                          const double* b, double* y, int opmask, bool has_b, bool mass, bool wv, bool wp);
 void launch_u_gs_inner(hipStream_t s, const ULev& L, USegs seg, double* x, const double* b);
+// A run of up to 16 interior colours (two bits each in seq, the first lowest)
+// in one launch, on levels with U.ipts.
+constexpr int kUCellN = 32;  // up to this many intervals per cell edge
+void launch_u_gs_cells(hipStream_t s, const ULevelData& U, unsigned seq, int steps, double* x, const double* b);
 // Free interface nodes [first, first + count) of one colour; maxocc: the
 // most occurrences of one of them (sets the lanes per node).
 void launch_u_gs_iface(hipStream_t s, const ULev& L, const UList& lst, int first, int count, int maxocc, double* x,

@@ -748,6 +748,15 @@ UHier* u_build(const double* xyz, int nv, const int* tet, int nt, const std::vec
       if (!zi.empty()) lv.zitems = USegs{upload(*u, zi), (int)zi.size(), 0, 64};
     }
     for (int r = 0; r < 4; ++r) lv.colour[r] = upload_segs(*u, H.cseg[r], H.lps_col);
+    if (const int n = lv.L.n; n >= 4 && n <= kUCellN) {
+      std::vector<int> pts;
+      for (int r = 0; r < 4; ++r) {
+        for (const int4& sg : H.cseg[r])
+          for (int q = 0; q < sg.w; ++q) pts.push_back(upack(sg.x + 4 * q, sg.y, sg.z));
+        lv.ioff[r + 1] = (int)pts.size();
+      }
+      lv.ipts = upload(*u, pts);
+    }
     lv.lst.off = upload(*u, lv.h_off);
     lv.lst.occ = upload(*u, lv.h_occ);
     lv.lst.ainv = upload(*u, H.ainv);
