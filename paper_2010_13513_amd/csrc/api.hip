@@ -912,8 +912,10 @@ void op_smooth(hhg_hier h, int l, T* x, const T* b, int iters, int gs, int xi, d
     } else {
       for (int s = 0; s < xi; ++s) {
         for (int c = 0; c < ncol; ++c) colour(c);
+        // the turn's colour is idempotent (its rows do not couple), except
+        // where it is rounded after each update
         if (sym)
-          for (int c = ncol - 1; c >= 0; --c) colour(c);
+          for (int c = ncol - (bf16_level ? 1 : 2); c >= 0; --c) colour(c);
       }
     }
     // r_p = g - B u + C p, then p -= omega D^{-1} r_p: the k-marching apply in

@@ -259,8 +259,11 @@ __global__ void __launch_bounds__(NT) k_gs_level(LevelConst<T> lc, T* __restrict
 #pragma unroll 1
   for (int s = 0; s < xi; ++s) {
     colours(relax);
+    // the turn's colour is idempotent and not repeated
     if (sym)
-      colours([&](auto cc) { relax(std::integral_constant<int, NC - 1 - decltype(cc)::value>{}); });
+      colours([&](auto cc) {
+        if constexpr (decltype(cc)::value > 0) relax(std::integral_constant<int, NC - 1 - decltype(cc)::value>{});
+      });
   }
   for (int c = tid; c < VS; c += NT) xd[c] = box[c];
 }

@@ -233,8 +233,12 @@ struct Cycle {
 #pragma unroll 1
           for (int s = 0; s < sc.xi; ++s) {
             colours(relax);
+            // the turn's colour is idempotent and not repeated
             if (sc.gs_sym)
-              colours([&](auto cc) { relax(std::integral_constant<int, S::NC - 1 - decltype(cc)::value>{}); });
+              colours([&](auto cc) {
+                if constexpr (decltype(cc)::value > 0)
+                  relax(std::integral_constant<int, S::NC - 1 - decltype(cc)::value>{});
+              });
           }
         }
         __syncthreads();
