@@ -892,13 +892,12 @@ __device__ __forceinline__ double node_row_len(const double* __restrict__ w, con
 // f - B^T p at free node q, component d.
 __device__ __forceinline__ double node_rhs(const UNodes& N, const unsigned* __restrict__ col, int d, int q, double f,
                                            const double* p) {
-  return f - node_row_len(N.BT + (size_t)d * N.len * N.n + q, col + q, N.n, q < N.off[N.ncol - 4] ? N.len : 16, p);
+  return f - node_row_len(N.BT + (size_t)d * N.len * N.n + q, col + q, N.n, N.rlen[q], p);
 }
 // B u (v = u_d, s = d < 3) or C p (s = 3) at node q.
 __device__ __forceinline__ double node_pres(const UNodes& N, const unsigned* __restrict__ col, int s, int q,
                                             const double* v) {
-  const bool inner = q >= N.off[N.ncol - 4] && q < N.off[N.ncol];
-  return node_row_len((s < 3 ? N.B + (size_t)s * N.len * N.n : N.C) + q, col + q, N.n, inner ? 16 : N.len, v);
+  return node_row_len((s < 3 ? N.B + (size_t)s * N.len * N.n : N.C) + q, col + q, N.n, N.rlen[q], v);
 }
 
 // The smallest levels: the whole call in one workgroup, u, p, f - B^T p and
@@ -919,18 +918,22 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
   double* const ai = lds + 8 * n;
   double* const la = lds + 9 * n;
   unsigned* const lc = reinterpret_cast<unsigned*>(la + (size_t)N.len * n);
-  int* const sched = reinterpret_cast<int*>(lc + (size_t)(N.len / 2) * n);  // one period: first | count << 12 | len << 24
+  int* const sched = reinterpret_cast<int*>(lc + (size_t)(N.len / 2) * n);  // one period: first | count << 12
+  unsigned short* const rl = reinterpret_cast<unsigned short*>(sched + 2 * kUNodeColours);
   const int per = sym ? 2 * N.ncol - 2 : N.ncol, total = xi * per + (sym ? 1 : 0);
   for (int t = tid; t < 4 * n; t += kUSmall) {
     const int f = t / n, q = t - f * n;
     u[t] = x[f * vs + N.own[q]];
   }
-  for (int t = tid; t < n; t += kUSmall) ai[t] = N.ainv[t];
+  for (int t = tid; t < n; t += kUSmall) {
+    ai[t] = N.ainv[t];
+    rl[t] = N.rlen[t];
+  }
   for (int t = tid; t < N.len * n; t += kUSmall) la[t] = N.A[t];
   for (int t = tid; t < N.len / 2 * n; t += kUSmall) lc[t] = N.col[t];
   if (tid < per) {
     const int c = tid < N.ncol ? tid : per - tid;
-    sched[tid] = N.off[c] | (N.off[c + 1] - N.off[c]) << 12 | N.clen[c] << 24;
+    sched[tid] = N.off[c] | (N.off[c + 1] - N.off[c]) << 12;
   }
   __syncthreads();
 #pragma unroll 1
@@ -945,8 +948,10 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
       const double* const gd = g + wave * n;
       double w[16];
       unsigned k[8];
+      int len = 16;  // of the prefetched row
       auto fetch = [&](int s) {
-        const int q = (s & 4095) + min(lane, max(((s >> 12) & 4095) - 1, 0));
+        const int q = (s & 4095) + min(lane, max((s >> 12) - 1, 0));
+        len = rl[q];
         node_cols<16>(lc + q, n, k);
 #pragma unroll
         for (int e = 0; e < 16; ++e) w[e] = la[e * n + q];
@@ -957,7 +962,7 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
       for (int st = 0; st < total; ++st) {
         r = r + 1 < per ? r + 1 : 0;
         const int s2 = sched[r];
-        const int q0 = s0 & 4095, m = (s0 >> 12) & 4095, len = s0 >> 24;
+        const int q0 = s0 & 4095, m = s0 >> 12, row = len;
         double a = 0.0, c = 0.0;
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
@@ -968,12 +973,12 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
         if (lane < m) {
           const int q = q0 + lane;
           a += c;
-          for (int e = 16; e < len; e += 8) a = node_row<8>(la + e * n + q, lc + (e / 2) * n + q, n, ud, a);
+          for (int e = 16; e < row; e += 8) a = node_row<8>(la + e * n + q, lc + (e / 2) * n + q, n, ud, a);
           ud[q] += (gd[q] - a) * ai[q];
         }
         for (int t = lane + 64; t < m; t += 64) {
           const int q = q0 + t;
-          ud[q] += (gd[q] - node_row_len(la + q, lc + q, n, len, ud)) * ai[q];
+          ud[q] += (gd[q] - node_row_len(la + q, lc + q, n, rl[q], ud)) * ai[q];
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1014,14 +1019,21 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
   double* const cw = lds + n;  // [cell][16]
   double* const xu = un + (size_t)blockIdx.x * n;
   const double* const g = gn + (size_t)blockIdx.x * n;
-  for (int t = tid; t < n; t += kUSweep) u[t] = xu[t];
+  for (int t0 = tid; t0 < n; t0 += 8 * kUSweep) {  // loads in batches
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = xu[min(t0 + q * kUSweep, n - 1)];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (t0 + q * kUSweep < n) u[t0 + q * kUSweep] = v[q];
+  }
   for (int t = tid; t < 16 * N.ncell; t += kUSweep) cw[t] = N.cellA[t];
   __syncthreads();
   // the update of a colour needs, besides u, words that no sweep changes:
   // they are loaded for the next colour before this colour's barrier
   double w[16], ai = 0.0, gq = 0.0;
   unsigned k[8];
-  int cl = 0;
+  int cl = 0, row = 16;
   auto fetch = [&](int c) {
     const int q = N.off[c] + tid;
     if (q < N.off[c + 1]) {
@@ -1029,7 +1041,9 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
       if (c < K) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) w[e] = N.A[e * n + q];
+        row = N.rlen[q];
       } else {
+        row = 16;
         cl = N.cell[q - in0];
       }
       ai = N.ainv[q];
@@ -1044,7 +1058,7 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
     const int c = r < N.ncol ? r : per - r;
     r = r + 1 < per ? r + 1 : 0;
     const int cn = r < N.ncol ? r : per - r;
-    const int q0 = N.off[c], m = N.off[c + 1] - q0, len = N.clen[c];
+    const int q0 = N.off[c], m = N.off[c + 1] - q0;
     double a = 0.0, a1 = 0.0;
     if (tid < m) {
       if (c >= K) {
@@ -1059,7 +1073,7 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
       }
       const int q = q0 + tid;
       a += a1;
-      for (int e = 16; e < len; e += 8) a = node_row<8>(N.A + e * n + q, N.col + (e / 2) * n + q, n, u, a);
+      for (int e = 16; e < row; e += 8) a = node_row<8>(N.A + e * n + q, N.col + (e / 2) * n + q, n, u, a);
       u[q] += (gq - a) * ai;
     }
     for (int t = tid + kUSweep; t < m; t += kUSweep) {
@@ -1073,7 +1087,7 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
 #pragma unroll
         for (int e = 0; e < 15; ++e) v = fma(wc[e], u[node_col(kk, e)], v);
       } else {
-        v = node_row_len(N.A + q, N.col + q, n, len, u);
+        v = node_row_len(N.A + q, N.col + q, n, N.rlen[q], u);
       }
       u[q] += (g[q] - v) * N.ainv[q];
     }
@@ -1228,7 +1242,7 @@ bool launch_u_smooth_nodes(hipStream_t s, const ULevelData& U, double* x, const 
   if (iters <= 0) return true;
   KScope ks(s, KF_SMALL, (double)slots);
   const size_t one = (size_t)N.n * (9 * sizeof(double) + N.len * (sizeof(double) + sizeof(unsigned) / 2)) +
-                     2 * kUNodeColours * sizeof(int);
+                     2 * kUNodeColours * sizeof(int) + (N.n + 3) / 4 * 8;
   if (one <= (size_t)kUNodeLds && N.n < 4096) {
     hipLaunchKernelGGL(k_u_smooth_nodes, dim3(1), dim3(kUSmall), one, s, N, vs, slots, x, b, iters, xi, (int)sym,
                        omega);

@@ -89,9 +89,10 @@ struct USegs {
 
 // A small level by nodes (each node once, no copies), for its smoothing calls:
 // local order = free interface nodes by colour, cell interiors by colour,
-// Dirichlet nodes.  Rows assembled over the cells, `len` entries each (a
-// multiple of 8, at least 16), entry-major ([e n + q]; unused entries: the
-// node itself with weight 0): A, B^T and B (three components each) and the
+// Dirichlet nodes; inside an interface colour the nodes of more than two cells
+// first.  Rows assembled over the cells, room for `len` entries each (a multiple
+// of 8, at least 16), entry-major ([e n + q]; unused entries: the node itself
+// with weight 0): A, B^T and B (three components each) and the
 // pressure block C; columns two to a word (entry 2 e in the low half of
 // col[e n + q]).  An interior node's entries are its 15 stencil points in
 // order, so its A weights are its cell's.  n = 0: the level has no tables.
@@ -100,7 +101,7 @@ constexpr int kUNodeColours = 64;
 struct UNodes {
   int n = 0, nfree = 0, len = 0, ncol = 0, ncell = 0;
   int off[kUNodeColours + 1];       // colour c: nodes off[c] .. off[c + 1]; the last four: cell interiors
-  int clen[kUNodeColours];          // its longest row, a multiple of 8, at least 16
+  const unsigned short* rlen = nullptr;  // entries of a node's row, rounded up to a multiple of 8, at least 16
   const unsigned* col = nullptr;
   const double *A = nullptr, *BT = nullptr, *B = nullptr, *C = nullptr;
   const double* cellA = nullptr;    // [cell][16] interior A rows (entry 15: 0)

@@ -625,7 +625,11 @@ void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
   auto iface = [&](int t) {
     occ.emplace_back(lv.h_occ.begin() + lv.h_off[t], lv.h_occ.begin() + lv.h_off[t + 1]);
   };
-  for (int t = 0; t < H.nfree; ++t) iface(t);
+  // nodes of many cells first, so that their long rows share a wavefront
+  for (int c = 0; c < lv.ncol_if; ++c)
+    for (const bool many : {true, false})
+      for (int t = lv.col_off[c]; t < lv.col_off[c + 1]; ++t)
+        if ((lv.h_off[t + 1] - lv.h_off[t] > 2) == many) iface(t);
   for (int c = 0; c <= lv.ncol_if; ++c) N.off[c] = lv.col_off[c];
   for (int c = 0; c < 4; ++c) {
     for (int cell = 0; cell < lv.L.ncell; ++cell)
@@ -668,11 +672,8 @@ void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
   }
   N.len = std::max(16, (int)(longest + 7) / 8 * 8);
   N.ncol = ncol;
-  for (int c = 0; c < ncol; ++c) {
-    size_t m = 1;
-    for (int q = N.off[c]; q < N.off[c + 1]; ++q) m = std::max(m, rows[q].size());
-    N.clen[c] = std::max(16, (int)(m + 7) / 8 * 8);
-  }
+  std::vector<unsigned short> rlen(nn);
+  for (int q = 0; q < nn; ++q) rlen[q] = (unsigned short)(std::max<size_t>(16, (rows[q].size() + 7) / 8 * 8));
   const size_t sz = (size_t)N.len * nn;
   std::vector<unsigned short> node(lv.L.vs, 0), cell;
   std::vector<unsigned> col(sz / 2, 0);
@@ -705,6 +706,7 @@ void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
   N.ncell = lv.L.ncell;
   N.cellA = upload(u, cellA);
   N.cell = upload(u, cell);
+  N.rlen = upload(u, rlen);
   N.work = upload(u, std::vector<double>(8 * (size_t)nn, 0.0));
   N.col = upload(u, col);
   N.A = upload(u, A);
