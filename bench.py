@@ -52,9 +52,9 @@ ALTERNATIVES = [((0, 1, 3, 1, 0, 3), "least work with gamma_u <= 2, gamma_p <= 1
 # (FETCH_SIZE x 2 + WRITE_SIZE, per dispatch, the calibration factor of a plain
 # copy applied); valid for the kernel code the summary names.
 TRAFFIC = {
-    "gs_edge_colour": {"bytes_per_launch": 3.0e6,
-                       "source": "profiles/fmg_p2p1_level5_cube.md: FETCH_SIZE x 2 + WRITE_SIZE per k_gs_edge "
-                                 "dispatch, weighted with the solve's launch mix over levels 3-5"},
+    "gs_edge_colour": {"bytes_per_launch": 7.9e6,
+                       "source": "profiles/fmg_p2p1_level5_cube.md: FETCH_SIZE x 2 + WRITE_SIZE per k_gs_level / "
+                                 "k_gs_box dispatch, weighted with the solve's launch mix over levels 3-5"},
 }
 APPLY_TRAFFIC = {"f64": 10.81e9, "f32": 4.66e9}   # profiles/apply_p2p1_48tets_level7.md
 # algorithmic bytes per work unit (float64 words), see the design doc
@@ -287,7 +287,8 @@ def main():
              "reference": f"FMG + V(3,3) cycles to rel. residual {stf.rel_res:.1e}"}
     log(f"[bench] relative error (Fourier forcing): delta_u {delta['delta_u']:.3e} delta_p {delta['delta_p']:.3e}")
 
-    # ---- roofline of the dominant kernel family (HIP events on the solve stream)
+    # ---- roofline of the dominant kernel family (HIP events on the solve stream);
+    # a run of several colours in one launch counts as gs_edge_colour
     fams = {hhg.KF_APPLY: "apply_residual", hhg.KF_PROW_BND: "boundary_pressure_rows",
             hhg.KF_GS_VERTEX: "gs_vertex_colour", hhg.KF_GS_EDGE: "gs_edge_colour", hhg.KF_PSTEP: "uzawa_pressure_step",
             hhg.KF_RESTRICT: "restrict", hhg.KF_PROLONG: "prolong", hhg.KF_COARSE: "coarse_gemv",
@@ -316,8 +317,7 @@ def main():
                 "traffic": traffic["bytes_per_launch"] if traffic else None,
                 "avg_launch_us": round(avg_ms * 1e3, 3), "bytes_per_launch": int(bytes_launch),
                 "launches_per_step": n_d, "share_of_step": round(ms_d / ms_step, 3),
-                "timing": ("HIP events stamped by each launch's dispatch packet (kernel start to end)"
-                           if dom.startswith("gs_") else "HIP events recorded around each launch")}
+                "timing": "HIP events recorded around each launch"}
     if traffic:
         roofline["traffic_source"] = traffic["source"]
 

@@ -713,21 +713,20 @@ void emit_sequence(FILE* f, const ElementSet& es, int G, const std::string& name
 }
 void emit_sequences(FILE* f, const ElementSet& es, int vorder) {
   if (vorder == 2) {
-    // contiguous colour ranges a..b, forward and backward; the two vertex
-    // colours stay in one run
-    for (int a = 0; a <= 8; ++a)
-      for (int b = a; b <= 8; ++b) {
-        if (a == 1 || b == 0) continue;
-        std::vector<int> fw, bw;
-        for (int c = a; c <= b; ++c) fw.push_back(c);
-        bw.assign(fw.rbegin(), fw.rend());
-        emit_sequence(f, es, 8, "P2Fwd" + std::to_string(a) + std::to_string(b), fw);
-        emit_sequence(f, es, 8, "P2Bwd" + std::to_string(b) + std::to_string(a), bw);
-      }
+    // the runs of colours a..b that launches take, forward and backward
+    const int runs[][2] = {{0, 1}, {2, 4}, {5, 8}, {0, 3}, {4, 8}};
+    for (const auto& r : runs) {
+      const int a = r[0], b = r[1];
+      std::vector<int> fw, bw;
+      for (int c = a; c <= b; ++c) fw.push_back(c);
+      bw.assign(fw.rbegin(), fw.rend());
+      emit_sequence(f, es, 8, "P2Fwd" + std::to_string(a) + std::to_string(b), fw);
+      emit_sequence(f, es, 8, "P2Bwd" + std::to_string(b) + std::to_string(a), bw);
+    }
   } else {
     // m colours in turn, starting with colour s
     for (int s = 0; s < 2; ++s)
-      for (int m = 1; m <= 6; ++m) {
+      for (int m = 1; m <= 4; ++m) {
         std::vector<int> q;
         for (int i = 0; i < m; ++i) q.push_back((s + i) & 1);
         emit_sequence(f, es, 1, "P1Seq" + std::to_string(s) + std::to_string(m), q);
