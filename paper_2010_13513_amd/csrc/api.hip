@@ -1279,17 +1279,31 @@ template <typename BL>
 void fmg_body(hhg_hier h, double* x, BL bl, const hhg_solver_params& p) {
   hipStream_t s = S(h);
   Level& top = h->L(h->lmax);
-  op_copy_boundary(h, h->lmax, x, top.w);
-  for (int l = h->lmax - 1; l >= h->lmin; --l) op_inject(h, l + 1, h->L(l + 1).w, h->L(l).w);
   Level& bot = h->L(h->lmin);
+  // Lattice without outflow faces: a level's boundary values come straight from
+  // x, whose own boundary no step writes; otherwise by injection, level by level.
+  const bool direct = !h->um && !h->nf && h->lmax > h->lmin;
+  auto finest = [&](int l) { return Finest<double>{x, top.g, h->lmax - l}; };
+  if (!direct) {
+    op_copy_boundary(h, h->lmax, x, top.w);
+    for (int l = h->lmax - 1; l >= h->lmin; --l) op_inject(h, l + 1, h->L(l + 1).w, h->L(l).w);
+  }
   launch_fill<double>(s, bot.xs, bot.vec_words, 0.0);
-  op_copy_boundary(h, h->lmin, bot.w, bot.xs);
+  if (direct)
+    launch_finest_boundary<double>(s, bot.g, finest(h->lmin), bot.xs);
+  else
+    op_copy_boundary(h, h->lmin, bot.w, bot.xs);
   op_coarse<double>(h, bot.xs, bl(h->lmin), true, &p);
   for (int l = h->lmin + 1; l <= h->lmax; ++l) {
     Level& lv = h->L(l);
     double* X = l == h->lmax ? x : lv.xs;
-    op_prolong<double>(h, l - 1, h->L(l - 1).xs, X, false, false);
-    op_copy_boundary(h, l, lv.w, X);
+    if (direct) {
+      launch_prolong<double>(s, h->L(l - 1).g, lv.g, ttables<double>(lv), h->L(l - 1).xs, X, false, true,
+                             l < h->lmax ? finest(l) : Finest<double>{});
+    } else {
+      op_prolong<double>(h, l - 1, h->L(l - 1).xs, X, false, false);
+      op_copy_boundary(h, l, lv.w, X);
+    }
     for (int c = 0; c < p.kappa; ++c) {
       vcycle(h, l, l, X, bl(l), p);
       op_mean_zero<double>(h, l, X);

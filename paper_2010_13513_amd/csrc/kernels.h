@@ -251,9 +251,22 @@ template <typename T>
 // threads (the coarse correction's start value), every word of the level.
 void launch_restrict(hipStream_t s, const Geom& gf, const Geom& gc, const TransferTables<T>* tt, const T* rf, T* rc,
                      T* zero_x = nullptr);
+// The finest level's vector as the source of Dirichlet values (no outflow
+// faces): a level `up` > 0 refinements below it has its boundary sites at
+// vertices there.
+template <typename T>
+struct Finest {
+  const T* x = nullptr;
+  Geom g{};
+  int up = 0;
+};
+// fin.x not null (plain interpolation, not add): the boundary velocity sites
+// take fin's values.
 template <typename T>
 void launch_prolong(hipStream_t s, const Geom& gc, const Geom& gf, const TransferTables<T>* tt, const T* xc, T* xf,
-                    bool add, bool skip_boundary);
+                    bool add, bool skip_boundary, const Finest<T>& fin = Finest<T>{});
+template <typename T>
+void launch_finest_boundary(hipStream_t s, const Geom& g, const Finest<T>& fin, T* dst);
 template <typename T>
 void launch_inject_boundary(hipStream_t s, const Geom& gf, const Geom& gc, const T* xf, T* xc);
 template <typename T>
