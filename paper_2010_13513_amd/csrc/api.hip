@@ -1152,12 +1152,14 @@ void op_coarse(hhg_hier h, T* x, const T* b, bool allow_mlp = true, const hhg_so
   op_mean_zero<T>(h, h->lmin, x);
 }
 
-// Variable V-cycle of Alg. fmg in storage/arithmetic precision T.
+// Variable V-cycle of Alg. fmg in storage/arithmetic precision T.  mean: with
+// the zero pressure mean of the result where the cycle's own launch can do it
+// (true: done; a solve's small levels otherwise take a launch of 4 us for it).
 template <typename T>
-void vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_params& p) {
+bool vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_params& p, bool mean = false) {
   if (l == h->lmin) {
     op_coarse<T>(h, x, b, true, &p);
-    return;
+    return false;
   }
   // the whole cycle from a small level down in one workgroup (plain exact
   // coarse solve only: no network, recorder, relaxation-only mode or pending
@@ -1186,8 +1188,10 @@ void vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_para
     int with = 0;  // levels above the coarsest with a viscosity
     for (int q = h->lmin + 1; q <= l; ++q) with += h->L(q).nu64 != nullptr;
     const int nu = with == 0 ? 0 : (with == l - h->lmin ? 1 : 2);
-    if (!launch_cycle_small<T>(S(h), slv<T>(h), sc, h->L(l).g.N, nu)) launch_vcycle_small<T>(S(h), slv<T>(h), sc);
-    return;
+    sc.mean = mean;
+    if (launch_cycle_small<T>(S(h), slv<T>(h), sc, h->L(l).g.N, nu)) return mean;
+    launch_vcycle_small<T>(S(h), slv<T>(h), sc);
+    return false;
   }
   Level& lv = h->L(l);
   Level& lc = h->L(l - 1);
@@ -1199,6 +1203,7 @@ void vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_para
   vcycle_t<T>(h, lf, l - 1, cxbuf<T>(lc), cbbuf<T>(lc), p);
   op_prolong<T>(h, l - 1, cxbuf<T>(lc), x, true, true);
   op_smooth<T>(h, l, x, b, p.nu_post + (lf - l) * p.nu_inc, p.gs, p.xi, om);
+  return false;
 }
 
 void vcycle(hhg_hier h, int lf, int l, double* x, const double* b, const hhg_solver_params& p) {
@@ -1304,16 +1309,12 @@ void fmg_body(hhg_hier h, double* x, BL bl, const hhg_solver_params& p) {
       op_prolong<double>(h, l - 1, h->L(l - 1).xs, X, false, false);
       op_copy_boundary(h, l, lv.w, X);
     }
-    for (int c = 0; c < p.kappa; ++c) {
-      vcycle(h, l, l, X, bl(l), p);
-      op_mean_zero<double>(h, l, X);
-    }
+    for (int c = 0; c < p.kappa; ++c)
+      if (!vcycle_t<double>(h, l, l, X, bl(l), p, true)) op_mean_zero<double>(h, l, X);
   }
   if (p.rtol <= 0.0)
-    for (int c = 0; c < p.extra_cycles; ++c) {
-      vcycle(h, h->lmax, h->lmax, x, bl(h->lmax), p);
-      op_mean_zero<double>(h, h->lmax, x);
-    }
+    for (int c = 0; c < p.extra_cycles; ++c)
+      if (!vcycle_t<double>(h, h->lmax, h->lmax, x, bl(h->lmax), p, true)) op_mean_zero<double>(h, h->lmax, x);
 }
 
 // The six Kuhn simplices of the cube [0,1]^3: vertices 0, e_a, e_a + e_b,

@@ -162,6 +162,7 @@ struct SmallCycle {
   int nunk;
   int lds_words;            // > 0: every level's vectors live in LDS (x, b copied in and x out)
   int q16;                  // levels lmin + q, q < q16, hold bfloat16 values (float32 only)
+  int mean;                 // launch_cycle_small: also the zero pressure mean of the result
 };
 // LDS available for the level vectors of the one-workgroup V-cycle (bytes).
 constexpr int kSmallLdsBytes = 128 * 1024;

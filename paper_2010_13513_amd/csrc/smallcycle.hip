@@ -512,6 +512,8 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
   __syncthreads();
   const Cycle<T, G, NTOP, NT, VAR> cy{lv, sc, box, red, tid, __builtin_amdgcn_readfirstlane(tid / 64), tid % 64};
   cy.template run<NTOP>(sc.nlev - 1);
+  __syncthreads();
+  if (sc.mean) cy.template shift<NTOP>(sc.nlev - 1, box + L::table + 3 * S::VS, 0);
   for (int t = tid; t < S::words; t += NT) sc.x[t] = box[L::table + t];
 }
 
