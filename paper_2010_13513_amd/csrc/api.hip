@@ -1152,15 +1152,29 @@ void op_coarse(hhg_hier h, T* x, const T* b, bool allow_mlp = true, const hhg_so
   op_mean_zero<T>(h, h->lmin, x);
 }
 
-// Variable V-cycle of Alg. fmg in storage/arithmetic precision T.  mean: with
-// the zero pressure mean of the result where the cycle's own launch can do it
-// (true: done; a solve's small levels otherwise take a launch of 4 us for it).
+// A step of an FMG solve: the cycle also takes the zero pressure mean where its
+// own launch can do it, and starts from the interpolation of xc (not null), the
+// vector of the level below, with the boundary values of fin, or of the vector
+// itself.
+struct FmgStep {
+  const double* xc = nullptr;
+  Finest<double> fin{};
+};
+// Variable V-cycle of Alg. fmg in storage/arithmetic precision T.  step (double
+// only): as above; true: the mean is done.
 template <typename T>
-bool vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_params& p, bool mean = false) {
+bool vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_params& p,
+              const FmgStep* step = nullptr) {
   if (l == h->lmin) {
     op_coarse<T>(h, x, b, true, &p);
     return false;
   }
+  auto interpolate = [&] {
+    if constexpr (std::is_same<T, double>::value)
+      if (step && step->xc)
+        launch_prolong<double>(S(h), h->L(l - 1).g, h->L(l).g, ttables<double>(h->L(l)), step->xc, x, false, true,
+                               step->fin);
+  };
   // the whole cycle from a small level down in one workgroup (plain exact
   // coarse solve only: no network, recorder, relaxation-only mode or pending
   // pseudo-inverse rebuild)
@@ -1188,8 +1202,14 @@ bool vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_para
     int with = 0;  // levels above the coarsest with a viscosity
     for (int q = h->lmin + 1; q <= l; ++q) with += h->L(q).nu64 != nullptr;
     const int nu = with == 0 ? 0 : (with == l - h->lmin ? 1 : 2);
-    sc.mean = mean;
-    if (launch_cycle_small<T>(S(h), slv<T>(h), sc, h->L(l).g.N, nu)) return mean;
+    if constexpr (std::is_same<T, double>::value)
+      if (step) {
+        sc.mean = 1;
+        sc.xc = step->xc;
+        sc.fx = step->fin.x, sc.fn1 = step->fin.g.n1, sc.fvs = step->fin.g.vstride, sc.fup = step->fin.up;
+      }
+    if (launch_cycle_small<T>(S(h), slv<T>(h), sc, h->L(l).g.N, nu)) return step != nullptr;
+    interpolate();
     launch_vcycle_small<T>(S(h), slv<T>(h), sc);
     return false;
   }
@@ -1197,6 +1217,7 @@ bool vcycle_t(hhg_hier h, int lf, int l, T* x, const T* b, const hhg_solver_para
   Level& lc = h->L(l - 1);
   const double om = 1.0 / p.omega_inv;
   T* r = rbuf<T>(lv);
+  interpolate();
   op_smooth<T>(h, l, x, b, p.nu_pre + (lf - l) * p.nu_inc, p.gs, p.xi, om);
   op_apply<T>(h, l, full_mask(h), x, b, r, true, true, true);
   op_restrict<T>(h, l, r, cbbuf<T>(lc), cxbuf<T>(lc));  // and the coarse start value 0
@@ -1302,19 +1323,21 @@ void fmg_body(hhg_hier h, double* x, BL bl, const hhg_solver_params& p) {
   for (int l = h->lmin + 1; l <= h->lmax; ++l) {
     Level& lv = h->L(l);
     double* X = l == h->lmax ? x : lv.xs;
+    FmgStep step;
     if (direct) {
-      launch_prolong<double>(s, h->L(l - 1).g, lv.g, ttables<double>(lv), h->L(l - 1).xs, X, false, true,
-                             l < h->lmax ? finest(l) : Finest<double>{});
+      step.xc = h->L(l - 1).xs;
+      if (l < h->lmax) step.fin = finest(l);
     } else {
       op_prolong<double>(h, l - 1, h->L(l - 1).xs, X, false, false);
       op_copy_boundary(h, l, lv.w, X);
     }
-    for (int c = 0; c < p.kappa; ++c)
-      if (!vcycle_t<double>(h, l, l, X, bl(l), p, true)) op_mean_zero<double>(h, l, X);
+    for (int c = 0; c < p.kappa; ++c, step = FmgStep{})
+      if (!vcycle_t<double>(h, l, l, X, bl(l), p, &step)) op_mean_zero<double>(h, l, X);
   }
   if (p.rtol <= 0.0)
     for (int c = 0; c < p.extra_cycles; ++c)
-      if (!vcycle_t<double>(h, h->lmax, h->lmax, x, bl(h->lmax), p, true)) op_mean_zero<double>(h, h->lmax, x);
+      if (const FmgStep step; !vcycle_t<double>(h, h->lmax, h->lmax, x, bl(h->lmax), p, &step))
+        op_mean_zero<double>(h, h->lmax, x);
 }
 
 // The six Kuhn simplices of the cube [0,1]^3: vertices 0, e_a, e_a + e_b,

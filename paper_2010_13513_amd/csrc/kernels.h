@@ -162,7 +162,14 @@ struct SmallCycle {
   int nunk;
   int lds_words;            // > 0: every level's vectors live in LDS (x, b copied in and x out)
   int q16;                  // levels lmin + q, q < q16, hold bfloat16 values (float32 only)
-  int mean;                 // launch_cycle_small: also the zero pressure mean of the result
+  // launch_cycle_small, a step of an FMG solve: the zero pressure mean of the
+  // result; xc: start from the interpolation of the level below (layout of
+  // ltop - 1) with the boundary values of x, or of the finest level's vector
+  // fx (fn1, fvs: its nodes per edge and component stride), fup refinements up
+  int mean;
+  const T* xc;
+  const T* fx;
+  int fn1, fvs, fup;
 };
 // LDS available for the level vectors of the one-workgroup V-cycle (bytes).
 constexpr int kSmallLdsBytes = 128 * 1024;

@@ -1048,16 +1048,6 @@ __device__ __forceinline__ void prolong_site(const Geom& gc, const Geom& gf, con
   for (int gr = 0; gr < G; ++gr) prolong_group<T, G>(gc, gf, tt, xc, xf, add, skip_boundary, t, i, j, k, gr);
   prolong_slice<T, G>(gc, gf, tt, xc, xf, add, skip_boundary, t, i, j, k, 3 * G);
 }
-// Velocity value of the finest level at site (i, j, k) of group gr of a level
-// `up` refinements below it (a vertex there): its slot in a component.
-template <int G>
-__device__ __forceinline__ int finest_slot(int gr, int i, int j, int k, int n1, int up) {
-  const int u = G == 1 ? up : up - 1;
-  const int X = (G == 1 ? i : 2 * i + gdx(gr)) << u, Y = (G == 1 ? j : 2 * j + gdy(gr)) << u,
-            Z = (G == 1 ? k : 2 * k + gdz(gr)) << u;
-  return X + n1 * (Y + n1 * Z);
-}
-
 // The boundary sites of a level take their values from the finest level's
 // vector (fin.x not null) instead of the interpolation: the chain of
 // injections and copies that it saves was two launches of 4 us per level (P1

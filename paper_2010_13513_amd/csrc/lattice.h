@@ -47,5 +47,15 @@ __device__ __forceinline__ bool vel_unknown(const Geom& g, int gr, int i, int j,
   return (f & ~g.nf) == 0;
 }
 
+// Velocity value of the finest level at site (i, j, k) of group gr of a level
+// `up` refinements below it (a vertex there): its slot in a component.
+template <int G>
+__device__ __forceinline__ int finest_slot(int gr, int i, int j, int k, int n1, int up) {
+  const int u = G == 1 ? up : up - 1;
+  const int X = (G == 1 ? i : 2 * i + gdx(gr)) << u, Y = (G == 1 ? j : 2 * j + gdy(gr)) << u,
+            Z = (G == 1 ? k : 2 * k + gdz(gr)) << u;
+  return X + n1 * (Y + n1 * Z);
+}
+
 }  // namespace
 }  // namespace hhg

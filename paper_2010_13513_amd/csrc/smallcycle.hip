@@ -494,10 +494,28 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
     const int cls = t / (n * m), es = t - cls * (n * m);
     box[es * 27 + cls] = (T)PRows<G>::w()[t];
   }
+  if (sc.xc) {
+    // an FMG step: boundary values, zero elsewhere, and the level below, whose
+    // interpolation is added after the barrier
+    using C = Shape<G, NTOP / 2>;
+    T* const xc = box + L::template xoff<NTOP / 2>();
 #pragma unroll 4
-  for (int t = tid; t < S::words; t += NT) {
-    box[L::table + t] = sc.x[t];
-    box[L::table + S::words + t] = sc.b[t];
+    for (int t = tid; t < S::words; t += NT) {
+      const int d = t / S::VS, r = t - d * S::VS, g = r / S::nn, q = r - g * S::nn;
+      const int i = q % S::S1, j = (q / S::S1) % S::S1, k = q / S::S2;
+      const bool bnd = d < 3 && vel_exists<G>(g, i, j, k, NTOP) && !vel_interior<G>(g, i, j, k, NTOP);
+      const T* from = sc.fx ? sc.fx + (size_t)d * sc.fvs + finest_slot<G>(g, i, j, k, sc.fn1, sc.fup) : sc.x + t;
+      box[L::table + t] = bnd ? *from : T(0);
+      box[L::table + S::words + t] = sc.b[t];
+    }
+#pragma unroll 4
+    for (int t = tid; t < C::words; t += NT) xc[t] = sc.xc[t];
+  } else {
+#pragma unroll 4
+    for (int t = tid; t < S::words; t += NT) {
+      box[L::table + t] = sc.x[t];
+      box[L::table + S::words + t] = sc.b[t];
+    }
   }
   if constexpr (VAR) {  // every level's viscosity above the coarsest
     auto load = [&](auto self, auto nc, int q) {
@@ -511,6 +529,7 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
   }
   __syncthreads();
   const Cycle<T, G, NTOP, NT, VAR> cy{lv, sc, box, red, tid, __builtin_amdgcn_readfirstlane(tid / 64), tid % 64};
+  if (sc.xc) cy.template prolong_from<NTOP>();
   cy.template run<NTOP>(sc.nlev - 1);
   __syncthreads();
   if (sc.mean) cy.template shift<NTOP>(sc.nlev - 1, box + L::table + 3 * S::VS, 0);
