@@ -103,8 +103,10 @@ struct Cycle {
   // Slice s of the pressure row at node t: B's component s, or (P1, s = 3)
   // the C row; weights at h = 1, table [entry][slice][class] (lanes of
   // different classes read different banks).  An entry outside the cube
-  // weighs zero and its address stays inside the LDS array (the table lies
-  // below the vectors, the residual above).
+  // weighs zero and meets a word that is finite unless one that some row uses
+  // is not: x's own, the table or the level above's viscosity or right-hand side
+  // of the pressure below them, for P1's C rows b's boundary sites above them
+  // (staged as zero).
   template <int N>
   __device__ __forceinline__ T prow_slice(const T* x, int t, int s) const {
     using S = Shape<G, N>;
@@ -494,6 +496,10 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
     const int cls = t / (n * m), es = t - cls * (n * m);
     box[es * 27 + cls] = (T)PRows<G>::w()[t];
   }
+  // b's word t; P1: zero for the words up to (0, 1, 1) of the first component, all
+  // on the boundary: no row uses them, and the C rows' entries above the cube
+  // meet them (Cycle::prow_slice; from the last pressure one step in i, j and k)
+  auto rhs = [&](int t) { return G == 1 && t <= S::S2 + S::S1 ? T(0) : sc.b[t]; };
   if (sc.xc) {
     // an FMG step: boundary values, zero elsewhere, and the level below, whose
     // interpolation is added after the barrier
@@ -506,7 +512,7 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
       const bool bnd = d < 3 && vel_exists<G>(g, i, j, k, NTOP) && !vel_interior<G>(g, i, j, k, NTOP);
       const T* from = sc.fx ? sc.fx + (size_t)d * sc.fvs + finest_slot<G>(g, i, j, k, sc.fn1, sc.fup) : sc.x + t;
       box[L::table + t] = bnd ? *from : T(0);
-      box[L::table + S::words + t] = sc.b[t];
+      box[L::table + S::words + t] = rhs(t);
     }
 #pragma unroll 4
     for (int t = tid; t < C::words; t += NT) xc[t] = sc.xc[t];
@@ -514,7 +520,7 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
 #pragma unroll 4
     for (int t = tid; t < S::words; t += NT) {
       box[L::table + t] = sc.x[t];
-      box[L::table + S::words + t] = sc.b[t];
+      box[L::table + S::words + t] = rhs(t);
     }
   }
   if constexpr (VAR) {  // every level's viscosity above the coarsest
