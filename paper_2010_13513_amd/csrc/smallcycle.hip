@@ -153,7 +153,7 @@ struct Cycle {
     }
   }
 
-  // iters Uzawa iterations on x, then (want_r) r = b - calA x, boundary
+  // iters >= 0 Uzawa iterations on x, then (want_r) r = b - calA x, boundary
   // velocity rows zero.  The sweeps of component d run on wavefronts d W ..
   // d W + W - 1 (W = Shape::waves), one site per thread and colour.
   template <int N>
@@ -546,10 +546,12 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
 
 // False (nothing launched) where the general kernel is needed: bfloat16
 // levels, a viscosity on some of the levels only (nu: 0 none, 1 all above the
-// coarsest, 2 mixed), other lattice sizes, more unknowns than threads.
+// coarsest, 2 mixed), other lattice sizes, more unknowns than threads, a count of
+// smoothing steps below zero on some level (taken as none there).
 template <typename T>
 bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc, int ntop, int nu) {
-  if (nu > 1 || sc.q16 > 0 || sc.nlev < 2) return false;
+  const int inc = min(0, (sc.nlev - 2) * sc.inc);  // of the lowest level above the coarsest
+  if (nu > 1 || sc.q16 > 0 || sc.nlev < 2 || sc.pre0 + inc < 0 || sc.post0 + inc < 0) return false;
 #define HHG_SMALL(G_, N_, NT_)                                                                  \
   if (sc.G == G_ && ntop == N_ && sc.nunk <= NT_) {                                             \
     KScope ks(s, KF_SMALL, sc.nlev);                                                            \
