@@ -1255,8 +1255,10 @@ bool launch_u_smooth_nodes(hipStream_t s, const ULevelData& U, double* x, const 
   const dim3 blk(kUBlock);
   hipLaunchKernelGGL(k_u_nodes_gather, dim3(ublocks(N.n)), blk, 0, s, N, vs, x);
   for (int it = 0; it < iters; ++it) {
-    hipLaunchKernelGGL(k_u_nodes_rhs, dim3(ublocks(N.nfree), 3), blk, 0, s, N, vs, b, p, g);
-    hipLaunchKernelGGL(k_u_nodes_sweep, dim3(3), dim3(kUSweep), lds, s, N, u, g, xi, (int)sym);
+    if (N.nfree > 0) {
+      hipLaunchKernelGGL(k_u_nodes_rhs, dim3(ublocks(N.nfree), 3), blk, 0, s, N, vs, b, p, g);
+      hipLaunchKernelGGL(k_u_nodes_sweep, dim3(3), dim3(kUSweep), lds, s, N, u, g, xi, (int)sym);
+    }
     hipLaunchKernelGGL(k_u_nodes_pres, dim3((N.n + 63) / 64), blk, 0, s, N, vs, b, u, p, pn, omega);
     std::swap(p, pn);
   }
