@@ -857,9 +857,8 @@ unsigned ublocks(long n) { return (unsigned)((n + kUBlock - 1) / kUBlock); }
 // cells, so a row is a batch of independent loads and one gather from LDS --
 // the cell-by-cell rows of the launch-per-colour path are three dependent
 // round trips per node and a launch per colour.
-constexpr int kUNodeLds = 160 * 1024 - 1024;  // dynamic LDS of one workgroup
 
-// E entries (E even) of a node's rows: columns.
+// E entries (E even) of a node's row, n words apart: columns.
 template <int E>
 __device__ __forceinline__ void node_cols(const unsigned* __restrict__ col, int n, unsigned (&k)[E / 2]) {
 #pragma unroll
@@ -881,23 +880,30 @@ __device__ __forceinline__ double node_row(const double* __restrict__ w, const u
   for (int e = 0; e < E; ++e) a = fma(we[e], v[node_col(k, e)], a);
   return a;
 }
-// Row of q over its first 16 entries and, below `more` entries, the rest.
-__device__ __forceinline__ double node_row_len(const double* __restrict__ w, const unsigned* __restrict__ col, int n,
-                                               int len, const double* v) {
-  double a = node_row<16>(w, col, n, v, 0.0);
+// The entries beyond the first 16 of a row of len entries with slice word x
+// (table w, columns col), added to a.
+__device__ __forceinline__ double node_more(const double* __restrict__ w, const unsigned* __restrict__ col, int n,
+                                            int len, unsigned x, const double* v, double a) {
+  w += 16 * n + x;
+  col += 8 * n + x / 16 * 8 + x % 16;
 #pragma unroll 1
-  for (int e = 16; e < len; e += 8) a = node_row<8>(w + e * n, col + (e / 2) * n, n, v, a);
+  for (int e = 16; e < len; e += 8, w += 128, col += 64) a = node_row<8>(w, col, 16, v, a);
   return a;
+}
+// Row of q (table w, columns col).
+__device__ __forceinline__ double node_row_len(const double* __restrict__ w, const unsigned* __restrict__ col, int n,
+                                               int q, int len, unsigned x, const double* v) {
+  return node_more(w, col, n, len, x, v, node_row<16>(w + q, col + q, n, v, 0.0));
 }
 // f - B^T p at free node q, component d.
 __device__ __forceinline__ double node_rhs(const UNodes& N, const unsigned* __restrict__ col, int d, int q, double f,
                                            const double* p) {
-  return f - node_row_len(N.BT + (size_t)d * N.len * N.n + q, col + q, N.n, N.rlen[q], p);
+  return f - node_row_len(N.BT + (size_t)d * N.sz, col, N.n, q, N.rlen[q], N.xoff[q], p);
 }
 // B u (v = u_d, s = d < 3) or C p (s = 3) at node q.
 __device__ __forceinline__ double node_pres(const UNodes& N, const unsigned* __restrict__ col, int s, int q,
                                             const double* v) {
-  return node_row_len((s < 3 ? N.B + (size_t)s * N.len * N.n : N.C) + q, col + q, N.n, N.rlen[q], v);
+  return node_row_len(s < 3 ? N.B + (size_t)s * N.sz : N.C, col, N.n, q, N.rlen[q], N.xoff[q], v);
 }
 
 // The smallest levels: the whole call in one workgroup, u, p, f - B^T p and
@@ -917,9 +923,10 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
   double* const g = lds + 4 * n;  // 4 n: f - B^T p / the pressure rows' parts
   double* const ai = lds + 8 * n;
   double* const la = lds + 9 * n;
-  unsigned* const lc = reinterpret_cast<unsigned*>(la + (size_t)N.len * n);
-  int* const sched = reinterpret_cast<int*>(lc + (size_t)(N.len / 2) * n);  // one period: first | count << 12
-  unsigned short* const rl = reinterpret_cast<unsigned short*>(sched + 2 * kUNodeColours);
+  unsigned* const lc = reinterpret_cast<unsigned*>(la + N.sz);
+  int* const sched = reinterpret_cast<int*>(lc + N.sz / 2);  // one period: first | count << 12
+  unsigned* const xo = reinterpret_cast<unsigned*>(sched + 2 * kUNodeColours);
+  unsigned short* const rl = reinterpret_cast<unsigned short*>(xo + n);
   const int per = sym ? 2 * N.ncol - 2 : N.ncol, total = xi * per + (sym ? 1 : 0);
   for (int t = tid; t < 4 * n; t += kUSmall) {
     const int f = t / n, q = t - f * n;
@@ -928,9 +935,10 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
   for (int t = tid; t < n; t += kUSmall) {
     ai[t] = N.ainv[t];
     rl[t] = N.rlen[t];
+    xo[t] = N.xoff[t];
   }
-  for (int t = tid; t < N.len * n; t += kUSmall) la[t] = N.A[t];
-  for (int t = tid; t < N.len / 2 * n; t += kUSmall) lc[t] = N.col[t];
+  for (int t = tid; t < N.sz; t += kUSmall) la[t] = N.A[t];
+  for (int t = tid; t < N.sz / 2; t += kUSmall) lc[t] = N.col[t];
   if (tid < per) {
     const int c = tid < N.ncol ? tid : per - tid;
     sched[tid] = N.off[c] | (N.off[c + 1] - N.off[c]) << 12;
@@ -973,12 +981,12 @@ __global__ void __launch_bounds__(kUSmall) k_u_smooth_nodes(UNodes N, long vs, l
         if (lane < m) {
           const int q = q0 + lane;
           a += c;
-          for (int e = 16; e < row; e += 8) a = node_row<8>(la + e * n + q, lc + (e / 2) * n + q, n, ud, a);
+          if (row > 16) a = node_more(la, lc, n, row, xo[q], ud, a);
           ud[q] += (gd[q] - a) * ai[q];
         }
         for (int t = lane + 64; t < m; t += 64) {
           const int q = q0 + t;
-          ud[q] += (gd[q] - node_row_len(la + q, lc + q, n, rl[q], ud)) * ai[q];
+          ud[q] += (gd[q] - node_row_len(la, lc, n, q, rl[q], xo[q], ud)) * ai[q];
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1034,6 +1042,7 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
   double w[16], ai = 0.0, gq = 0.0;
   unsigned k[8];
   int cl = 0, row = 16;
+  unsigned xo = 0;
   auto fetch = [&](int c) {
     const int q = N.off[c] + tid;
     if (q < N.off[c + 1]) {
@@ -1042,6 +1051,7 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
 #pragma unroll
         for (int e = 0; e < 16; ++e) w[e] = N.A[e * n + q];
         row = N.rlen[q];
+        xo = N.xoff[q];
       } else {
         row = 16;
         cl = N.cell[q - in0];
@@ -1073,7 +1083,7 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
       }
       const int q = q0 + tid;
       a += a1;
-      for (int e = 16; e < row; e += 8) a = node_row<8>(N.A + e * n + q, N.col + (e / 2) * n + q, n, u, a);
+      if (row > 16) a = node_more(N.A, N.col, n, row, xo, u, a);
       u[q] += (gq - a) * ai;
     }
     for (int t = tid + kUSweep; t < m; t += kUSweep) {
@@ -1087,7 +1097,7 @@ __global__ void __launch_bounds__(kUSweep) k_u_nodes_sweep(UNodes N, double* __r
 #pragma unroll
         for (int e = 0; e < 15; ++e) v = fma(wc[e], u[node_col(kk, e)], v);
       } else {
-        v = node_row_len(N.A + q, N.col + q, n, N.rlen[q], u);
+        v = node_row_len(N.A, N.col, n, q, N.rlen[q], N.xoff[q], u);
       }
       u[q] += (g[q] - v) * N.ainv[q];
     }
@@ -1241,15 +1251,12 @@ bool launch_u_smooth_nodes(hipStream_t s, const ULevelData& U, double* x, const 
   if (N.n == 0) return false;
   if (iters <= 0) return true;
   KScope ks(s, KF_SMALL, (double)slots);
-  const size_t one = (size_t)N.n * (9 * sizeof(double) + N.len * (sizeof(double) + sizeof(unsigned) / 2)) +
-                     2 * kUNodeColours * sizeof(int) + (N.n + 3) / 4 * 8;
-  if (one <= (size_t)kUNodeLds && N.n < 4096) {
-    hipLaunchKernelGGL(k_u_smooth_nodes, dim3(1), dim3(kUSmall), one, s, N, vs, slots, x, b, iters, xi, (int)sym,
-                       omega);
+  if (u_nodes_one(N.n, N.sz)) {
+    hipLaunchKernelGGL(k_u_smooth_nodes, dim3(1), dim3(kUSmall), u_nodes_lds(N.n, N.sz), s, N, vs, slots, x, b, iters,
+                       xi, (int)sym, omega);
     return true;
   }
-  const size_t lds = ((size_t)N.n + 16 * N.ncell) * sizeof(double);
-  if (lds > (size_t)kUNodeLds) return false;
+  const size_t lds = u_nodes_sweep_lds(N.n, N.ncell);
   const size_t n = N.n;
   double *u = N.work, *p = u + 3 * n, *pn = u + 4 * n, *g = u + 5 * n;
   const dim3 blk(kUBlock);

@@ -90,18 +90,24 @@ struct USegs {
 // A small level by nodes (each node once, no copies), for its smoothing calls:
 // local order = free interface nodes by colour, cell interiors by colour,
 // Dirichlet nodes; inside an interface colour the nodes of more than two cells
-// first.  Rows assembled over the cells, room for `len` entries each (a multiple
-// of 8, at least 16), entry-major ([e n + q]; unused entries: the node itself
-// with weight 0): A, B^T and B (three components each) and the
-// pressure block C; columns two to a word (entry 2 e in the low half of
-// col[e n + q]).  An interior node's entries are its 15 stencil points in
-// order, so its A weights are its cell's.  n = 0: the level has no tables.
+// first.  Rows assembled over the cells.  The first 16 entries of every row are
+// entry-major ([e n + q]); the entries beyond, which the nodes of several cells
+// have, follow in slices of 16 such nodes, each slice to its longest row (entry
+// e of the node with slice word x = xoff[q] at [16 n + x + 16 (e - 16)]), so
+// that a node in hundreds of cells takes the memory of its own slice.  Unused
+// entries: the node itself with weight 0.  Tables A, B^T and B (three components
+// each, `sz` words apart) and the pressure block C; columns two to a word (entry
+// 2 e in the low half: [e n + q], [8 n + x / 16 8 + x % 16 + 16 (e - 8)]).  An
+// interior node's entries are its 15 stencil points in order, so its A weights
+// are its cell's.  n = 0: the level has no tables.
 constexpr int kUNodeMax = 20000;
 constexpr int kUNodeColours = 64;
+constexpr int kUNodeLds = 160 * 1024 - 1024;  // dynamic LDS of one workgroup
 struct UNodes {
-  int n = 0, nfree = 0, len = 0, ncol = 0, ncell = 0;
+  int n = 0, nfree = 0, sz = 0, ncol = 0, ncell = 0;
   int off[kUNodeColours + 1];       // colour c: nodes off[c] .. off[c + 1]; the last four: cell interiors
   const unsigned short* rlen = nullptr;  // entries of a node's row, rounded up to a multiple of 8, at least 16
+  const unsigned* xoff = nullptr;
   const unsigned* col = nullptr;
   const double *A = nullptr, *BT = nullptr, *B = nullptr, *C = nullptr;
   const double* cellA = nullptr;    // [cell][16] interior A rows (entry 15: 0)
@@ -111,6 +117,17 @@ struct UNodes {
   const unsigned short* node = nullptr;  // node of a slot
   double* work = nullptr;                // 8 n: velocity (3), pressure (2), f - B^T p (3)
 };
+// LDS bytes of the whole call in one workgroup (u, p, f - B^T p, A^{-1}, A's rows
+// and their columns, the colours of a period, xoff and rlen), and of the sweeps
+// of one component (u and the cells' interior rows).
+constexpr size_t u_nodes_lds(int n, int sz) {
+  return (size_t)n * 9 * sizeof(double) + (size_t)sz * (sizeof(double) + sizeof(unsigned) / 2) +
+         2 * kUNodeColours * sizeof(int) + (size_t)n * sizeof(unsigned) + (size_t)(n + 3) / 4 * 8;
+}
+constexpr size_t u_nodes_sweep_lds(int n, int ncell) { return ((size_t)n + 16 * (size_t)ncell) * sizeof(double); }
+// The one-workgroup form holds n < 4096 (a colour's first node and count in one
+// word).
+constexpr bool u_nodes_one(int n, int sz) { return n < 4096 && u_nodes_lds(n, sz) <= (size_t)kUNodeLds; }
 
 // Host-side state of one level of an unstructured hierarchy.
 struct ULevelData {

@@ -610,7 +610,9 @@ void u_level_host(const UMeshPrims& M, const double* xyz, int l, int schur, ULev
 // Node tables of a small level (UNodes): assembled rows of every node.
 void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
   const int n = lv.L.n, nn = lv.nnodes, ncol = lv.ncol_if + 4;
-  if (nn > kUNodeMax || ncol > kUNodeColours || lv.L.ncell > 4096) return;
+  // only for levels that a launch takes (a row has at least 16 entries)
+  const bool sweeps = u_nodes_sweep_lds(nn, lv.L.ncell) <= (size_t)kUNodeLds;
+  if (nn > kUNodeMax || ncol > kUNodeColours || lv.L.ncell > 4096 || !(sweeps || u_nodes_one(nn, 16 * nn))) return;
   UNodes& N = lv.nodes;
   struct Entry {
     int r;
@@ -648,7 +650,7 @@ void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
     local[H.canon[own[q]]] = q;
   }
   std::vector<std::vector<Entry>> rows(nn);
-  size_t longest = 1;
+  std::vector<int> last(nn, -1), at(nn);  // the row that holds a column last, and where
   for (int q = 0; q < nn; ++q) {
     for (const int2& o : occ[q]) {
       const int i = o.y & 1023, j = (o.y >> 10) & 1023, k = o.y >> 20, m = uclass(i, j, k, n);
@@ -656,10 +658,11 @@ void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
       for (int e = 0; e < kUPoints; ++e) {
         if (!((cs.inside[m] >> e) & 1)) continue;
         const int r = local[H.canon[(long)o.x * lv.L.P + uslot(i + udir(e, 0), j + udir(e, 1), k + udir(e, 2), n)]];
-        size_t w = 0;
-        while (w < rows[q].size() && rows[q][w].r != r) ++w;
-        if (w == rows[q].size()) rows[q].push_back(Entry{r, 0.0, {0, 0, 0}, {0, 0, 0}, 0.0});
-        Entry& en = rows[q][w];
+        if (last[r] != q) {
+          last[r] = q, at[r] = (int)rows[q].size();
+          rows[q].push_back(Entry{r, 0.0, {0, 0, 0}, {0, 0, 0}, 0.0});
+        }
+        Entry& en = rows[q][at[r]];
         en.a += cs.A[m][e];
         en.c += cs.cfac * cs.A[m][e];
         for (int d = 0; d < 3; ++d) {
@@ -668,31 +671,50 @@ void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
         }
       }
     }
-    longest = std::max(longest, rows[q].size());
   }
-  N.len = std::max(16, (int)(longest + 7) / 8 * 8);
-  N.ncol = ncol;
+  // the slices of the entries beyond 16
   std::vector<unsigned short> rlen(nn);
-  for (int q = 0; q < nn; ++q) rlen[q] = (unsigned short)(std::max<size_t>(16, (rows[q].size() + 7) / 8 * 8));
-  const size_t sz = (size_t)N.len * nn;
+  std::vector<unsigned> xoff(nn, 0);
+  std::vector<int> lng, room(nn, 16);  // nodes with such entries; entries that a node has room for
+  for (int q = 0; q < nn; ++q) {
+    rlen[q] = (unsigned short)(std::max<size_t>(16, (rows[q].size() + 7) / 8 * 8));
+    if (rlen[q] > 16) lng.push_back(q);
+  }
+  size_t sz = 16 * (size_t)nn;
+  for (size_t first = 0; first < lng.size(); first += 16) {
+    const size_t end = std::min(first + 16, lng.size());
+    int len = 0;
+    for (size_t w = first; w < end; ++w) len = std::max(len, (int)rlen[lng[w]]);
+    for (size_t w = first; w < end; ++w) {
+      xoff[lng[w]] = (unsigned)(sz - 16 * (size_t)nn + (w - first));
+      room[lng[w]] = len;
+    }
+    sz += 16 * (size_t)(len - 16);
+  }
+  HHG_REQUIRE(sz < (1u << 28), HHG_ERR_ARG, "unstructured mesh: a node in too many cells");
+  if (!sweeps && !u_nodes_one(nn, (int)sz)) return;
+  N.sz = (int)sz;
+  N.ncol = ncol;
   std::vector<unsigned short> node(lv.L.vs, 0), cell;
   std::vector<unsigned> col(sz / 2, 0);
-  auto set_col = [&](int e, int q, int r) { col[(size_t)(e / 2) * nn + q] |= (unsigned)r << (e & 1 ? 16 : 0); };
   std::vector<double> A(sz, 0.0), BT(3 * sz, 0.0), B(3 * sz, 0.0), C(sz, 0.0), ainv(nn, 0.0), dinv(nn);
   for (int q = 0; q < nn; ++q) {
-    for (int e = 0; e < N.len; ++e) {
-      const size_t at = (size_t)e * nn + q;
+    const size_t x = xoff[q], xc = x / 16 * 8 + x % 16;
+    for (int e = 0; e < room[q]; ++e) {
+      const size_t w = e < 16 ? (size_t)e * nn + q : 16 * ((size_t)nn + e - 16) + x;
+      unsigned& c = col[e < 16 ? (size_t)(e / 2) * nn + q : 8 * (size_t)nn + xc + 16 * (size_t)(e / 2 - 8)];
+      const int half = e & 1 ? 16 : 0;
       if (e >= (int)rows[q].size()) {
-        set_col(e, q, q);
+        c |= (unsigned)q << half;
         continue;
       }
       const Entry& en = rows[q][e];
-      set_col(e, q, en.r);
-      A[at] = en.a;
-      C[at] = en.c;
+      c |= (unsigned)en.r << half;
+      A[w] = en.a;
+      C[w] = en.c;
       for (int d = 0; d < 3; ++d) {
-        BT[d * sz + at] = en.bt[d];
-        B[d * sz + at] = en.b[d];
+        BT[d * sz + w] = en.bt[d];
+        B[d * sz + w] = en.b[d];
       }
       if (en.r == q && q < N.nfree) ainv[q] = 1.0 / en.a;
     }
@@ -707,6 +729,7 @@ void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
   N.cellA = upload(u, cellA);
   N.cell = upload(u, cell);
   N.rlen = upload(u, rlen);
+  N.xoff = upload(u, xoff);
   N.work = upload(u, std::vector<double>(8 * (size_t)nn, 0.0));
   N.col = upload(u, col);
   N.A = upload(u, A);

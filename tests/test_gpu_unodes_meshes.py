@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2010_13513_amd import hhg
-from tests.gpu_util import Lib, block_errors
+from tests.gpu_util import Lib, block_errors, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -46,6 +46,25 @@ def test_smoothing_on_a_fan(cells, L, gs, xi, iters):
         # rows of up to about 800 entries, carried over at most 4 sweeps: under 4000 roundings
         eu, ep = block_errors(lib, L, got, want)
         assert eu <= 1e-12 and ep <= 1e-12, (eu, ep)
+    finally:
+        lib.close()
+
+
+def test_tables_hold_the_rows_that_are_there():
+    """150 cells around an edge at levels 2 and 3: 21014 nodes, all but the
+    fourteen on the edge with 15 to 24 entries.  An entry takes 66 bytes, so
+    the tables are below 21014 x 24 x 66 bytes = 34 MB; the other arrays of the
+    hierarchy are below 26 MB, and each of at most 100 allocations may take 2 MB
+    more than its size.  Rows of the longest one's length: 440 MB."""
+    torch = torch_cuda()
+    torch.cuda.synchronize()
+    first = torch.cuda.mem_get_info()[0]
+    lib = Lib(hhg.HHG_P1P1, 2, 3, mesh=fan(150))
+    try:
+        torch.cuda.synchronize()
+        used = first - torch.cuda.mem_get_info()[0]
+        print(f"[tables] {used / 1e6:.1f} MB", flush=True)
+        assert used <= 260e6
     finally:
         lib.close()
 
