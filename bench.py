@@ -317,7 +317,8 @@ def main():
                 "traffic": traffic["bytes_per_launch"] if traffic else None,
                 "avg_launch_us": round(avg_ms * 1e3, 3), "bytes_per_launch": int(bytes_launch),
                 "launches_per_step": n_d, "share_of_step": round(ms_d / ms_step, 3),
-                "timing": "HIP events recorded around each launch"}
+                "timing": ("HIP events stamped by each launch's dispatch packet (kernel start to end)"
+                           if dom.startswith("gs_") else "HIP events recorded around each launch")}
     if traffic:
         roofline["traffic_source"] = traffic["source"]
 

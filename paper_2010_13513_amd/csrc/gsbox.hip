@@ -489,16 +489,18 @@ __global__ void __launch_bounds__((MarchShape<Q, TX, TY>::NT))
 
 }  // namespace
 
-// Sites that a run updates (the timer's work units).
+// Sites of colour c (the timer's work units): a vertex colour has the sites of
+// one parity, (i + j + k) mod 2 = c, of an odd number per axis.
+double colour_sites(const Geom& g, int c) {
+  const int gr = c < kGsVertexColours ? 0 : c - kGsVertexColours + 1;
+  double n = 1.0;
+  for (int a = 0; a < 3; ++a) n *= g.N - 1 + gdir(g.G, gr, a);
+  return c < kGsVertexColours ? (n + 2 * c - 1) / 2 : n;
+}
 template <typename Q>
 double run_sites(const Geom& g) {
   double sites = 0;
-  for (int q = 0; q < Q::n; ++q) {
-    const int gr = Q::col[q] < kGsVertexColours ? 0 : Q::col[q] - kGsVertexColours + 1;
-    double n = Q::col[q] < kGsVertexColours ? 0.5 : 1.0;
-    for (int a = 0; a < 3; ++a) n *= g.N - 1 + gdir(Q::G, gr, a);
-    sites += n;
-  }
+  for (int q = 0; q < Q::n; ++q) sites += colour_sites(g, Q::col[q]);
   return sites;
 }
 
@@ -511,15 +513,14 @@ void launch_gs_run(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, 
     while ((1 << l) < v) ++l;
     return l;
   };
-  KScope ks(s, Q::G == 1 ? KF_GS_VERTEX : KF_GS_EDGE, run_sites<Q>(g));
+  KScope ks(s, Q::G == 1 ? KF_GS_VERTEX : KF_GS_EDGE, run_sites<Q>(g), true);
   const TileGrid tg{log2i(g.N / TX), log2i(g.N / TY), log2i(g.N / TZ)};
   const dim3 grid(3 << (tg.lx + tg.ly + tg.lz));
   if (lc.nu)
-    hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT, true>), grid, dim3(NT), 0, s, g, lc, x, alt, x, alt, p, b,
-                       in_alt, tg);
+    launch_timed(ks, k_gs_box<T, Q, TX, TY, TZ, NT, true>, grid, dim3(NT), s, g, lc, x, alt, x, alt, p, b, in_alt, tg);
   else
-    hipLaunchKernelGGL((k_gs_box<T, Q, TX, TY, TZ, NT, false>), grid, dim3(NT), 0, s, g, lc, x, alt, x, alt, p, b,
-                       in_alt, tg);
+    launch_timed(ks, k_gs_box<T, Q, TX, TY, TZ, NT, false>, grid, dim3(NT), s, g, lc, x, alt, x, alt, p, b, in_alt,
+                 tg);
   for (int gr = 0; gr < Q::G; ++gr) in_alt ^= (unsigned)Q::wr[gr] << gr;
 }
 
@@ -533,7 +534,7 @@ void launch_gs_march(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x
     while ((1 << l) < v) ++l;
     return l;
   };
-  KScope ks(s, Q::G == 1 ? KF_GS_VERTEX : KF_GS_EDGE, run_sites<Q>(g));
+  KScope ks(s, Q::G == 1 ? KF_GS_VERTEX : KF_GS_EDGE, run_sites<Q>(g), true);
   const int ltx = log2i(g.N / TX), lty = log2i(g.N / TY);
   // planes per workgroup: the fewest iterations in turn, with the planes that
   // a range marches besides its own (a workgroup per CU; where LDS holds two,
@@ -549,8 +550,8 @@ void launch_gs_march(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x
   const int nch = (g.n1 + kc - 1) / kc, blocks = (tiles * nch + 7) & ~7;
   // the groups a run writes are all in the same buffer
   T* out = (in_alt >> Sh::wgroup(0)) & 1u ? x : alt;
-  hipLaunchKernelGGL((k_gs_march<T, Q, TX, TY>), dim3(blocks), dim3(Sh::NT), 0, s, g, lc, x, alt, out, p, b, in_alt,
-                     ltx, lty, kc);
+  launch_timed(ks, k_gs_march<T, Q, TX, TY>, dim3(blocks), dim3(Sh::NT), s, g, lc, x, alt, out, p, b, in_alt, ltx, lty,
+               kc);
   for (int gr = 0; gr < Q::G; ++gr) in_alt ^= (unsigned)Q::wr[gr] << gr;
 }
 
@@ -663,14 +664,16 @@ bool gs_level_supported(const Geom& g, int xi, bool sym) {
 template <typename T>
 void launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* p, const T* b, int xi,
                      bool sym) {
-  const double m = (g.G == 1 ? g.N : 2 * g.N) - 1;
-  KScope ks(s, KF_GS_EDGE, m * m * m * xi * (sym ? 2 : 1));
-#define HHG_LEVEL(G_, N_, NT_)                                                                                      \
-  if (g.G == G_ && g.N == N_) {                                                                                     \
-    if (lc.nu)                                                                                                      \
-      hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_, true>), dim3(3), dim3(NT_), 0, s, lc, x, p, b, xi, (int)sym); \
-    else                                                                                                            \
-      hipLaunchKernelGGL((k_gs_level<T, G_, N_, NT_, false>), dim3(3), dim3(NT_), 0, s, lc, x, p, b, xi, (int)sym); \
+  const int last = gs_colours(g.G) - 1;  // taken once by a symmetric sweep
+  double sweep = sym ? -colour_sites(g, last) : 0.0;
+  for (int c = 0; c <= last; ++c) sweep += (sym ? 2 : 1) * colour_sites(g, c);
+  KScope ks(s, g.G == 1 ? KF_GS_VERTEX : KF_GS_EDGE, sweep * xi, true);
+#define HHG_LEVEL(G_, N_, NT_)                                                                              \
+  if (g.G == G_ && g.N == N_) {                                                                             \
+    if (lc.nu)                                                                                              \
+      launch_timed(ks, k_gs_level<T, G_, N_, NT_, true>, dim3(3), dim3(NT_), s, lc, x, p, b, xi, (int)sym);  \
+    else                                                                                                    \
+      launch_timed(ks, k_gs_level<T, G_, N_, NT_, false>, dim3(3), dim3(NT_), s, lc, x, p, b, xi, (int)sym); \
   }
   HHG_LEVEL(8, 8, 512)
   HHG_LEVEL(8, 4, 128)

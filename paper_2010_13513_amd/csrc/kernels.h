@@ -1,5 +1,7 @@
 // Kernel-side declarations shared by the launchers (host) and kernels.hip.
 #pragma once
+#include <hip/hip_ext.h>
+
 #include "hhg_internal.h"
 
 namespace hhg {
@@ -113,6 +115,14 @@ struct KScope {
   KScope(hipStream_t s, int fam, double units, bool packet = false);
   ~KScope();
 };
+// Launch, with the packet-stamped events of a KScope opened with packet = true.
+template <typename K, typename... Args>
+void launch_timed(const KScope& ks, K kernel, dim3 grid, dim3 block, hipStream_t s, Args... args) {
+  if (ks.packet_)
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ks.a_, ks.b_, 0, args...);
+  else
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
+}
 // Sum of event-measured durations (ms), launches and work units of one family
 // since the last read; synchronises the recorded events.
 void timer_read(int family, double* total_ms, int* launches, double* units);

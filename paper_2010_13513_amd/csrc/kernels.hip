@@ -9,7 +9,6 @@
 #include <type_traits>
 #include <vector>
 
-#include <hip/hip_ext.h>
 
 #include "kernels.h"
 #include "lanes.h"
@@ -2018,15 +2017,6 @@ void launch_uzawa_pressure(hipStream_t s, const Geom& g, const LevelConst<T>& lc
   LevelConst<T> c = lc;
   c.nu = c.ainv_site = nullptr;
   apply_launch<T>(s, g, c, x, b, r, g.G == 1 ? 15 : 7, true, false, true, bnd, nbnd, ps);
-}
-
-// Launch, with the packet-stamped events of a KScope opened with packet = true.
-template <typename K, typename... Args>
-void launch_timed(const KScope& ks, K kernel, dim3 grid, dim3 block, hipStream_t s, Args... args) {
-  if (ks.packet_)
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ks.a_, ks.b_, 0, args...);
-  else
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
 }
 
 template <typename T>
