@@ -324,6 +324,14 @@ struct MarchShape {
     return q;
   }
   static constexpr int pro = q0() + 2 - Q::blo[2];  // planes in the ring before it
+  // what the ring's length and the write-back rely on: no step is further behind
+  // than the last, and the planes before the first iteration fit the ring
+  static constexpr int most() {
+    int m = 0;
+    for (int s = 0; s < Q::n; ++s) m = m > Q::skew[s] ? m : Q::skew[s];
+    return m;
+  }
+  static_assert(last == most() && pro >= 1 && pro <= W, "ring of planes");
 };
 
 // The march of the wavefronts of colour s.
@@ -549,10 +557,13 @@ void launch_gs_march(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x
   }
   const int nch = (g.n1 + kc - 1) / kc, blocks = (tiles * nch + 7) & ~7;
   // the groups a run writes are all in the same buffer
+  unsigned wr = 0;
+  for (int gr = 0; gr < Q::G; ++gr) wr |= (unsigned)Q::wr[gr] << gr;
+  HHG_REQUIRE((in_alt & wr) == 0 || (in_alt & wr) == wr, HHG_ERR_STATE, "internal: groups of a run in two buffers");
   T* out = (in_alt >> Sh::wgroup(0)) & 1u ? x : alt;
   launch_timed(ks, k_gs_march<T, Q, TX, TY>, dim3(blocks), dim3(Sh::NT), s, g, lc, x, alt, out, p, b, in_alt, ltx, lty,
                kc);
-  for (int gr = 0; gr < Q::G; ++gr) in_alt ^= (unsigned)Q::wr[gr] << gr;
+  in_alt ^= wr;
 }
 
 template <typename T>
