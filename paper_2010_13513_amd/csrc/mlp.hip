@@ -117,8 +117,11 @@ __device__ __forceinline__ v4f gemm_tile(const GemmOp& o, int tm, int tn, bool r
     const int k = 32 * full + 8 * kg;
     product(load8(arow, k, o.K), load8(brow, k, o.K));
   }
-  // the wait states between the last product and the first read of its result:
-  // the compiler's own were missing on a branch taken right after a product
+  // the wait states between the last product and the first read of its result,
+  // 16 where 8 are needed (4 passes + 4): the compiler's own were missing on a
+  // branch taken right after a product (results of rows 2 and 3 of 4 stale), so
+  // no branch but the loop's and the tail's follows one (a row sum's is before
+  // it), and both lead here.  The assembly is checked by tests/test_mfma_waits.py.
   asm volatile("s_nop 15" : "+a"(acc));
   if (rsum) {  // sum over the four k lane groups of row r
     asum += __shfl_xor(asum, 16);
