@@ -619,13 +619,13 @@ void emit_box_rows(FILE* f, const ElementSet& es, const char* D, int G) {
 }
 
 // A run of Gauss-Seidel colours done on one box of the lattice (overlapped
-// tiles): `seq` lists the colours in order.  With the tile [0, t) per axis as
-// the sites whose final values are wanted, step s has to update its group on
-// [lo[s], t + hi[s]) -- wider than the tile where later steps read its
-// neighbours -- and group g has to be loaded on [glo, t + ghi), the pressure on
-// [plo, t + phi); all follow from the rows' offsets, backwards from the last
-// step.  wr[g]: the run updates group g; first[s]: vertex colours come in two
-// halves (parity par[s]).
+// tiles): `seq` lists the colours in order, col[n].  With the tile [0, t) per
+// axis as the sites whose final values are wanted, step s has to update its
+// group on [lo[s], t + hi[s]) -- wider than the tile where later steps read its
+// neighbours -- and the box [blo, t + bhi) holds every word that a row of the run
+// reads (velocities, pressure, vertex viscosities); all follow from the rows'
+// offsets, backwards from the last step.  wr[g]: the run updates group g;
+// skew[s]: planes that step s is behind when the steps march along k together.
 void emit_sequence(FILE* f, const ElementSet& es, int G, const std::string& name, const std::vector<int>& seq) {
   struct Box {
     bool any = false;
@@ -698,18 +698,14 @@ void emit_sequence(FILE* f, const ElementSet& es, int G, const std::string& name
   for (int c : seq) std::fprintf(f, "%d, ", c);
   std::fprintf(f, "};\n  static constexpr int wr[%d] = {", G);
   for (int g = 0; g < G; ++g) std::fprintf(f, "%d, ", wr[g]);
-  std::fprintf(f, "};\n  static constexpr int used[%d] = {", G);
-  for (int g = 0; g < G; ++g) std::fprintf(f, "%d, ", need[g].any ? 1 : 0);
   std::fprintf(f, "};\n");
   std::fprintf(f, "  static constexpr int skew[%zu] = {", skew.size());
   for (int z : skew) std::fprintf(f, "%d, ", z);
   std::fprintf(f, "};\n");
   table("lo", step, false);
   table("hi", step, true);
-  table("glo", need, false);
-  table("ghi", need, true);
-  std::fprintf(f, "  static constexpr int plo[3] = %s, phi[3] = %s, blo[3] = %s, bhi[3] = %s;\n};\n", arr(pb.lo).c_str(),
-               arr(pb.hi).c_str(), arr(all.lo).c_str(), arr(all.hi).c_str());
+  std::fprintf(f, "  static constexpr int blo[3] = %s, bhi[3] = %s;\n};\n", arr(all.lo).c_str(),
+               arr(all.hi).c_str());
 }
 void emit_sequences(FILE* f, const ElementSet& es, int vorder) {
   if (vorder == 2) {
@@ -724,9 +720,9 @@ void emit_sequences(FILE* f, const ElementSet& es, int vorder) {
       emit_sequence(f, es, 8, "P2Bwd" + std::to_string(b) + std::to_string(a), bw);
     }
   } else {
-    // m colours in turn, starting with colour s
+    // m colours in turn, starting with colour s (the runs that launches take)
     for (int s = 0; s < 2; ++s)
-      for (int m = 1; m <= 4; ++m) {
+      for (int m = s == 0 ? 1 : 2; m <= (s == 0 ? 4 : 3); ++m) {
         std::vector<int> q;
         for (int i = 0; i < m; ++i) q.push_back((s + i) & 1);
         emit_sequence(f, es, 1, "P1Seq" + std::to_string(s) + std::to_string(m), q);

@@ -610,19 +610,24 @@ void launch_gs_runs(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x,
     const int runs = (total + most - 1) / most;
     for (int done = 0, r = 0; r < runs; ++r) {
       const int len = (total - done + runs - r - 1) / (runs - r);
-#define HHG_P1(S_, L_)                                                                 \
-  if ((done & 1) == S_ && len == L_) {                                                 \
-    if (along_k) {                                                                     \
-      if constexpr (L_ <= 3) HHG_MARCH(P1Seq##S_##L_, 128 / (int)sizeof(T), 2 * (int)sizeof(T)); \
-    } else if (g.N == 32) {                                                            \
-      if constexpr (L_ <= 3) HHG_RUN(P1Seq##S_##L_, 8, 8, 8, 512);                     \
-    } else {                                                                           \
-      if constexpr (L_ <= 2 || sizeof(T) == 4) HHG_RUN(P1Seq##S_##L_, 16, 8, 8, 512);  \
-    }                                                                                  \
+      // the runs that the cuts make (those of one colour start at colour 0, those
+      // of four too)
+      bool launched = false;
+#define HHG_P1(S_, L_)                                                                  \
+  if ((done & 1) == S_ && len == L_) {                                                  \
+    if (along_k) {                                                                      \
+      if constexpr (L_ <= 3 && (L_ > 1 || sizeof(T) == 8))                              \
+        launched = true, HHG_MARCH(P1Seq##S_##L_, 128 / (int)sizeof(T), 2 * (int)sizeof(T)); \
+    } else if (g.N == 32) {                                                             \
+      if constexpr (L_ == 2 || L_ == 3) launched = true, HHG_RUN(P1Seq##S_##L_, 8, 8, 8, 512); \
+    } else {                                                                            \
+      if constexpr (sizeof(T) == 8 ? S_ == 0 && L_ <= 2 : L_ > 1)                       \
+        launched = true, HHG_RUN(P1Seq##S_##L_, 16, 8, 8, 512);                         \
+    }                                                                                   \
   }
-      HHG_P1(0, 1) HHG_P1(0, 2) HHG_P1(0, 3) HHG_P1(0, 4)
-      HHG_P1(1, 1) HHG_P1(1, 2) HHG_P1(1, 3) HHG_P1(1, 4)
+      HHG_P1(0, 1) HHG_P1(0, 2) HHG_P1(0, 3) HHG_P1(0, 4) HHG_P1(1, 2) HHG_P1(1, 3)
 #undef HHG_P1
+      HHG_REQUIRE(launched, HHG_ERR_STATE, "internal: no kernel for a run of colours");
       done += len;
     }
     return;
