@@ -54,18 +54,23 @@ struct Shape {
   // wavefronts per velocity component in the sweeps (every colour in one pass)
   static constexpr int waves = most() == 0 ? 1 : (most() + 63) / 64;
 };
+// Intervals of the smallest lattice of a hierarchy (Taylor-Hood on one interval
+// is refused at creation).
+template <int G>
+constexpr int kSmallest = G == 1 ? 1 : 2;
 // LDS layout: the weight table, then [x | b] (and the vertex viscosities when
-// they vary) of every level from the top down to N = 1, then one residual
-// vector of the top level's size.
+// they vary) of every level from the top down to the smallest lattice, then one
+// residual vector of the top level's size.
 template <int G, int NTOP, bool VAR>
 struct Layout {
+  static constexpr int NMIN = kSmallest<G>;
   static constexpr int table = 27 * PRows<G>::n * PRows<G>::m;
   template <int N>
   static constexpr int xoff() {
     if constexpr (N >= NTOP) return table;
     else return xoff<2 * N>() + 2 * Shape<G, 2 * N>::words + (VAR ? Shape<G, 2 * N>::nn : 0);
   }
-  static constexpr int roff = xoff<1>() + 2 * Shape<G, 1>::words + (VAR ? Shape<G, 1>::nn : 0);
+  static constexpr int roff = xoff<NMIN>() + 2 * Shape<G, NMIN>::words + (VAR ? Shape<G, NMIN>::nn : 0);
   static constexpr int words = roff + Shape<G, NTOP>::words;
 };
 
@@ -468,17 +473,19 @@ struct Cycle {
 
   template <int N>
   __device__ __forceinline__ void run(int q) const {
-    if constexpr (N >= 2) {
-      const int below = sc.nlev - 1 - q;
-      smooth<N>(q, sc.pre0 + below * sc.inc, true);
-      restrict_to<N>(q);
+    const int below = sc.nlev - 1 - q;
+    smooth<N>(q, sc.pre0 + below * sc.inc, true);
+    restrict_to<N>(q);
+    if constexpr (N / 2 == kSmallest<G>) {
+      coarse<N / 2>();  // q == 1 (host-checked)
+    } else {
       if (q == 1)
         coarse<N / 2>();
       else
         run<N / 2>(q - 1);
-      prolong_from<N>();
-      smooth<N>(q, sc.post0 + below * sc.inc, false);
     }
+    prolong_from<N>();
+    smooth<N>(q, sc.post0 + below * sc.inc, false);
   }
 };
 
@@ -528,7 +535,7 @@ __global__ void __launch_bounds__(NT) k_cycle_small(const SmallLevel<T>* __restr
       constexpr int N = decltype(nc)::value;
       T* nu = box + L::template xoff<N>() + 2 * Shape<G, N>::words;
       for (int t = tid; t < Shape<G, N>::nn; t += NT) nu[t] = lv[q].lc.nu[t];
-      if constexpr (N > 1)
+      if constexpr (N / 2 > kSmallest<G>)
         if (q > 1) self(self, std::integral_constant<int, N / 2>{}, q - 1);
     };
     load(load, std::integral_constant<int, NTOP>{}, sc.nlev - 1);
@@ -552,6 +559,7 @@ template <typename T>
 bool launch_cycle_small(hipStream_t s, const SmallLevel<T>* lv, const SmallCycle<T>& sc, int ntop, int nu) {
   const int inc = min(0, (sc.nlev - 2) * sc.inc);  // of the lowest level above the coarsest
   if (nu > 1 || sc.q16 > 0 || sc.nlev < 2 || sc.pre0 + inc < 0 || sc.post0 + inc < 0) return false;
+  if ((ntop >> (sc.nlev - 1)) < (sc.G == 1 ? kSmallest<1> : kSmallest<8>)) return false;  // run's recursion
 #define HHG_SMALL(G_, N_, NT_)                                                                  \
   if (sc.G == G_ && ntop == N_ && sc.nunk <= NT_) {                                             \
     KScope ks(s, KF_SMALL, sc.nlev);                                                            \
