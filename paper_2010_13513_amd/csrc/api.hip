@@ -897,8 +897,9 @@ void op_smooth(hhg_hier h, int l, T* x, const T* b, int iters, int gs, int xi, d
   // alternates too (p_alt), so that its step needs no launch of its own.
   const bool sym = gs == HHG_GS_SYM;
   const bool bf16_level = std::is_same<T, float>::value && l - h->lmin < h->bf16_levels;
-  const bool runs = !bf16_level && gs_runs_supported<T>(lv.g, lv.nu64 != nullptr, xi, sym);
-  const bool whole = !bf16_level && !runs && gs_level_supported(lv.g, xi, sym);
+  const bool varnu = lv.nu64 != nullptr;
+  const bool runs = !bf16_level && gs_runs_supported<T>(lv.g, varnu, iters, xi, sym);
+  const bool whole = !bf16_level && !runs && gs_level_supported<T>(lv.g, varnu, xi, sym);
   const bool fused = !bf16_level && (h->disc == HHG_P2P1 || runs || whole);
   const size_t vs3 = 3 * (size_t)lv.g.vstride;
   unsigned in_alt = 0;

@@ -524,8 +524,11 @@ void launch_gs_run(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, 
   KScope ks(s, Q::G == 1 ? KF_GS_VERTEX : KF_GS_EDGE, run_sites<Q>(g), true);
   const TileGrid tg{log2i(g.N / TX), log2i(g.N / TY), log2i(g.N / TZ)};
   const dim3 grid(3 << (tg.lx + tg.ly + tg.lz));
-  if (lc.nu)
-    launch_timed(ks, k_gs_box<T, Q, TX, TY, TZ, NT, true>, grid, dim3(NT), s, g, lc, x, alt, x, alt, p, b, in_alt, tg);
+  constexpr bool with_nu = !(Q::G == 1 && Q::n > 3);  // no run of four with a viscosity
+  HHG_REQUIRE(with_nu || !lc.nu, HHG_ERR_STATE, "internal: no kernel for a run of colours");
+  if (with_nu && lc.nu)
+    launch_timed(ks, k_gs_box<T, Q, TX, TY, TZ, NT, with_nu>, grid, dim3(NT), s, g, lc, x, alt, x, alt, p, b, in_alt,
+                 tg);
   else
     launch_timed(ks, k_gs_box<T, Q, TX, TY, TZ, NT, false>, grid, dim3(NT), s, g, lc, x, alt, x, alt, p, b, in_alt,
                  tg);
@@ -567,10 +570,15 @@ void launch_gs_march(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x
 }
 
 template <typename T>
-bool gs_runs_supported(const Geom& g, bool varnu, int xi, bool sym) {
+bool gs_runs_supported(const Geom& g, bool varnu, int iters, int xi, bool sym) {
   if (g.nf != 0) return false;
   const bool sweeps = xi * (sym ? 2 : 1) > 1;
-  if (g.G == 1) return g.N == 32 || (g.N == 64 && sweeps) || g.N > 64;
+  if (g.G == 1) {
+    // one float64 iteration of forward sweeps with a viscosity gains less than
+    // its copy back costs (below)
+    if (varnu && sizeof(T) == 8 && iters == 1 && !sym && (g.N == 64 || (g.N == 128 && xi == 1))) return false;
+    return g.N == 32 || (g.N == 64 && sweeps) || g.N > 64;
+  }
   return g.N == 16 || g.N == 32 || (!varnu && (g.N > 64 || (g.N == 64 && sizeof(T) == 8 && sweeps)));
 }
 
@@ -597,7 +605,12 @@ bool gs_runs_supported(const Geom& g, bool varnu, int xi, bool sym) {
 // (along k on 16 x 16 / 32 x 8 tiles, runs of two at N = 128 in float64, else
 // of three; boxes 246 / 170 and 2406 / 1384).  One forward sweep at N = 64 is
 // two launches either way with the copy back (28.1 against 28.6 us): a launch
-// per colour there.  Variable viscosity: on boxes at every size.
+// per colour there.  Variable viscosity: on boxes at every size, the runs of at
+// most three from N = 64 on in float32 (with the viscosity a run of four fills
+// the LDS and the registers: two sweeps at N = 128, a launch per colour 177 us,
+// one run of four 222, two of two 156).  One float64 iteration of forward
+// sweeps at N = 64 (three: 61.9 against 65.3 us) and of one at N = 128 (171
+// against 179) keeps a launch per colour, two and more (124 against 120) do not.
 template <typename T>
 void launch_gs_runs(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* p, const T* b,
                     int xi, bool sym, unsigned& in_alt) {
@@ -606,7 +619,8 @@ void launch_gs_runs(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x,
   if (g.G == 1) {
     const bool along_k = g.N > 64 && !lc.nu;
     const int total = sym ? 2 * xi + 1 : 2 * xi;
-    const int most = g.N == 32 ? 3 : (along_k ? (sizeof(T) == 4 || g.N > 128 ? 3 : 2) : (sizeof(T) == 4 ? 4 : 2));
+    const bool f64 = sizeof(T) == 8;
+    const int most = g.N == 32 ? 3 : (along_k ? (f64 && g.N == 128 ? 2 : 3) : (f64 ? 2 : (lc.nu ? 3 : 4)));
     const int runs = (total + most - 1) / most;
     for (int done = 0, r = 0; r < runs; ++r) {
       const int len = (total - done + runs - r - 1) / (runs - r);
@@ -672,10 +686,16 @@ void launch_gs_runs(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x,
 
 // Taylor-Hood N <= 8 and P1 N <= 16; P1 N = 16 with one sweep of two colours
 // costs less as two launches than the load and write-back around it (smoothing
-// call 14.6 against 17.6 us; two sweeps 21.5 against 15.6 us).
-bool gs_level_supported(const Geom& g, int xi, bool sym) {
+// call 14.6 against 17.6 us; two sweeps 21.5 against 15.6 us).  With a viscosity
+// its element rows on 1024 threads gain in float32 from three sweeps on (call
+// 27.2 -> 23.8 us; two sweeps three times 54.7 -> 57.1), in float64 never (three
+// sweeps 29.7 -> 32.8, symmetric 19.1 -> 24.5).
+template <typename T>
+bool gs_level_supported(const Geom& g, bool varnu, int xi, bool sym) {
   if (g.nf != 0) return false;
-  return g.G == 8 ? g.N == 4 || g.N == 8 : g.N == 8 || (g.N == 16 && xi * (sym ? 2 : 1) > 1);
+  if (g.G == 8) return g.N == 4 || g.N == 8;
+  const int sweeps = xi * (sym ? 2 : 1);
+  return g.N == 8 || (g.N == 16 && (varnu ? sizeof(T) == 4 && sweeps > 2 : sweeps > 1));
 }
 template <typename T>
 void launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, const T* p, const T* b, int xi,
@@ -686,8 +706,9 @@ void launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x
   KScope ks(s, g.G == 1 ? KF_GS_VERTEX : KF_GS_EDGE, sweep * xi, true);
 #define HHG_LEVEL(G_, N_, NT_)                                                                              \
   if (g.G == G_ && g.N == N_) {                                                                             \
-    if (lc.nu)                                                                                              \
-      launch_timed(ks, k_gs_level<T, G_, N_, NT_, true>, dim3(3), dim3(NT_), s, lc, x, p, b, xi, (int)sym);  \
+    constexpr bool with_nu = !(G_ == 1 && N_ == 16 && sizeof(T) == 8); /* gs_level_supported */             \
+    if (with_nu && lc.nu)                                                                                   \
+      launch_timed(ks, k_gs_level<T, G_, N_, NT_, with_nu>, dim3(3), dim3(NT_), s, lc, x, p, b, xi, (int)sym); \
     else                                                                                                    \
       launch_timed(ks, k_gs_level<T, G_, N_, NT_, false>, dim3(3), dim3(NT_), s, lc, x, p, b, xi, (int)sym); \
   }
@@ -699,7 +720,8 @@ void launch_gs_level(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x
 }
 
 #define HHG_INSTANTIATE(T)                                                                                          \
-  template bool gs_runs_supported<T>(const Geom&, bool, int, bool);                                                 \
+  template bool gs_runs_supported<T>(const Geom&, bool, int, int, bool);                                            \
+  template bool gs_level_supported<T>(const Geom&, bool, int, bool);                                                \
   template void launch_gs_level<T>(hipStream_t, const Geom&, const LevelConst<T>&, T*, const T*, const T*, int,    \
                                    bool);                                                                           \
   template void launch_gs_runs<T>(hipStream_t, const Geom&, const LevelConst<T>&, T*, T*, const T*, const T*, int,  \

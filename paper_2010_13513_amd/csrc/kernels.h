@@ -223,8 +223,9 @@ void launch_gs_colour(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* 
 // in_alt: group g is in alt; all bits equal between calls).  Level: the same
 // in place, one launch.  p: the pressures.
 template <typename T>
-bool gs_runs_supported(const Geom& g, bool varnu, int xi, bool sym);
-bool gs_level_supported(const Geom& g, int xi, bool sym);
+bool gs_runs_supported(const Geom& g, bool varnu, int iters, int xi, bool sym);
+template <typename T>
+bool gs_level_supported(const Geom& g, bool varnu, int xi, bool sym);
 template <typename T>
 void launch_gs_runs(hipStream_t s, const Geom& g, const LevelConst<T>& lc, T* x, T* alt, const T* p, const T* b,
                     int xi, bool sym, unsigned& in_alt);
