@@ -773,7 +773,7 @@ UHier* u_build(const double* xyz, int nv, const int* tet, int nt, const std::vec
       if (!zi.empty()) lv.zitems = USegs{upload(*u, zi), (int)zi.size(), 0, 64};
     }
     for (int r = 0; r < 4; ++r) lv.colour[r] = upload_segs(*u, H.cseg[r], H.lps_col);
-    if (const int n = lv.L.n; n >= 4 && n <= kUCellN) {
+    if (const int n = lv.L.n; n >= kUCellMin && n <= kUCellN) {
       std::vector<int> pts;
       for (int r = 0; r < 4; ++r) {
         for (const int4& sg : H.cseg[r])
