@@ -900,7 +900,10 @@ void op_smooth(hhg_hier h, int l, T* x, const T* b, int iters, int gs, int xi, d
   const bool varnu = lv.nu64 != nullptr;
   const bool runs = !bf16_level && gs_runs_supported<T>(lv.g, varnu, iters, xi, sym);
   const bool whole = !bf16_level && !runs && gs_level_supported<T>(lv.g, varnu, xi, sym);
-  const bool fused = !bf16_level && (h->disc == HHG_P2P1 || runs || whole);
+  // Taylor-Hood float32 with a viscosity from N = 128 on: the pressure rows by
+  // sites and the step apart (below)
+  const bool by_sites = bf16_level || (varnu && h->disc == HHG_P2P1 && sizeof(T) == 4 && lv.g.N >= 128);
+  const bool fused = !by_sites && (h->disc == HHG_P2P1 || runs || whole);
   const size_t vs3 = 3 * (size_t)lv.g.vstride;
   unsigned in_alt = 0;
   bool p_alt = false;
@@ -924,7 +927,10 @@ void op_smooth(hhg_hier h, int l, T* x, const T* b, int iters, int gs, int xi, d
     // rows written).  The step is applied by that launch itself -- in place for
     // Taylor-Hood, whose pressure rows read no p (C = 0) -- except where the
     // residual is rounded to bfloat16 first or p has to stay in place.  The
-    // rows do not depend on the viscosity.
+    // rows do not depend on the viscosity; with one, the rows by sites and the
+    // step apart are the faster form in float32 at N = 128 (per iteration of one
+    // sweep 769 -> 752 us; N = 64 105 against 118 us, float64 at N = 128 1529
+    // against 1535).
     PStep<T> ps;
     ps.dinv = dinv<T>(lv);
     ps.omega = (T)omega;
@@ -933,11 +939,11 @@ void op_smooth(hhg_hier h, int l, T* x, const T* b, int iters, int gs, int xi, d
       ps.p = p;
       ps.pout = (p_alt ? r : x) + vs3;
       launch_uzawa_pressure<T>(S(h), lv.g, lconst<T>(lv), in_alt ? r : x, b, r, lv.bnd, lv.nbnd, ps);
-    } else if (!bf16_level) {
+    } else if (!by_sites) {
       launch_uzawa_pressure<T>(S(h), lv.g, lconst<T>(lv), x, b, r, lv.bnd, lv.nbnd, ps);  // r_p alone
       launch_pressure_step<T>(S(h), lv.g, dinv<T>(lv), x, r, (T)omega);
     } else {
-      op_apply<T>(h, l, full_mask(h) & (lv.nu64 ? 12 : 15), x, b, r, true, false, true);
+      op_apply<T>(h, l, full_mask(h) & (varnu ? 12 : 15), x, b, r, true, false, true);
       launch_pressure_step<T>(S(h), lv.g, dinv<T>(lv), x, r, (T)omega);
       round_out<T>(h, l, x, 0, vs3, lv.g.nn, 1);
     }
