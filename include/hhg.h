@@ -420,9 +420,11 @@ hhg_status hhg_coarse_pair(hhg_hier h, const double* r, float* features, float* 
  * off.  On an unstructured macro mesh the same bound is on a level's slots
  * (cells times points per cell) and applies to every smoothing call
  * (hhg_smooth and the smoothing inside cycles) on levels of at most 20000
- * nodes: the call runs on assembled rows of the nodes in one workgroup, or
- * one per velocity component, instead of a launch per colour (same updates
- * in the same order, the sums of a row in another order); default 30000. */
+ * nodes and 60 interface colours that fit a workgroup's LDS (nodes + 16 cells
+ * below 20352, or a few hundred nodes): the call runs on assembled rows of the
+ * nodes in one workgroup, or one per velocity component, instead of a launch
+ * per colour (same updates in the same order, the sums of a row in another
+ * order); default 30000. */
 hhg_status hhg_hier_set_fused_sites(hhg_hier h, long max_sites);
 /* Not in the paper: bfloat16 storage on the coarse levels of float32
  * cycles.  The n coarsest levels (lmin .. lmin + n - 1, 0 <= n <= number of

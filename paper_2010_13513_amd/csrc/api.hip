@@ -139,9 +139,10 @@ constexpr size_t kScratchBytes = kScratchEpochs * sizeof(double) + kScratchOrder
 // Default bound of the node-table smoothing calls on unstructured meshes
 // (slots of a level; hhg_hier_set_fused_sites): every level that has the
 // tables gains.  FMG(2,3,2,1,A_s,1) on the cube benchmark to level 6, with
-// them up to no level 26.3 ms, level 1 22.9, 2 18.5, 3 14.8, 4 13.4; per Uzawa
-// iteration (A_s, xi = 1) level 1 69 -> 11 us, 2 130 -> 18, 3 145 -> 32, 4 165
-// -> 80.
+// them up to no level 22.2 ms, level 1 18.8, 2 14.5, 3 12.1, 4 11.4; per Uzawa
+// iteration (A_s, xi = 1) by launches and by tables, level 1 50 and 11 us, 2 84
+// and 18, 3 90 and 33, 4 95 and 72; 162 cells 86 and 16, 99 and 32, 118 and 82;
+// 200 cells around an edge, level 2, 214 and 106.
 constexpr long kUFusedSlots = 30000;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 

@@ -583,7 +583,7 @@ bool gs_runs_supported(const Geom& g, bool varnu, int iters, int xi, bool sym) {
 }
 
 // Taylor-Hood.  Variable viscosity takes the same runs (float32 V(3,3) with three
-// sweeps to N = 64: 4.29 -> 3.15 ms).  Measured per Uzawa iteration with three
+// sweeps to N = 64: 4.29 -> 3.00 ms).  Measured per Uzawa iteration with three
 // forward sweeps (float64 / float32, constant coefficients), against a launch
 // per colour: N = 16 105 -> 49 / 100 -> 42 us with two runs on 4^3 tiles (three
 // runs: 53 / 48; 8 x 4 x 4 tiles: 57 / 48), N = 32 125 -> 101 / 110 -> 77 us with

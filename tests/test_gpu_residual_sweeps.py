@@ -42,7 +42,7 @@ def _diagonal(lib, L, G, n1, ijk, varnu):
     return diag
 
 
-@pytest.mark.parametrize("gs,xi", [(FWD, 3), (FWD, 2), (SYM, 2)])
+@pytest.mark.parametrize("gs,xi", [(FWD, 3), (FWD, 2), (FWD, 1), (SYM, 2)])
 @pytest.mark.parametrize("disc,L,varnu", [(P1, 7, True), (P1, 7, False), (P2, 6, False), (P2, 7, False)])
 def test_matches_residual_sweeps(disc, L, varnu, gs, xi):
     n1, G = 2 ** L + 1, 1 if disc == P1 else 8
