@@ -102,6 +102,7 @@ struct USegs {
 // are its cell's.  n = 0: the level has no tables.
 constexpr int kUNodeMax = 20000;
 constexpr int kUNodeColours = 64;
+constexpr int kUNodeEntries = 1 << 22;  // of a level's tables: 277 MB (24 cells, level 4: 2.9e5)
 constexpr int kUNodeLds = 160 * 1024 - 1024;  // dynamic LDS of one workgroup
 struct UNodes {
   int n = 0, nfree = 0, sz = 0, ncol = 0, ncell = 0;

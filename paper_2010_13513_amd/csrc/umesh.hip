@@ -691,8 +691,7 @@ void build_nodes(UHier& u, ULevelData& lv, const UHostLevel& H) {
     }
     sz += 16 * (size_t)(len - 16);
   }
-  HHG_REQUIRE(sz < (1u << 28), HHG_ERR_ARG, "unstructured mesh: a node in too many cells");
-  if (!sweeps && !u_nodes_one(nn, (int)sz)) return;
+  if (sz > (size_t)kUNodeEntries || (!sweeps && !u_nodes_one(nn, (int)sz))) return;
   N.sz = (int)sz;
   N.ncol = ncol;
   std::vector<unsigned short> node(lv.L.vs, 0), cell;
